@@ -85,8 +85,9 @@ const char *ssn_status_string(int status);
  * (and, when k % 8 != 0, every n % 8 == 0); and float32 storage for
  * compress / project_grad / compress_projected / decompress with d % 64 == 0
  * and U rows of 1 to 128 floats (k, or ldu of a zero-padded basis), and
- * project_weights with d % 32 == 0, k <= 128 and every n % 4 == 0, on
- * float32 MFMA (float32 products and accumulation).  Everything else runs
+ * project_weights with d % 32 == 0, k <= 128 and every n % 4 == 0, on the
+ * matrix cores at float32 accuracy (float32 products, or operands split
+ * exactly into three bf16 planes; float32 accumulation).  Everything else runs
  * the generic kernels (fp32 arithmetic, one wavefront per token / one block
  * per column).
  */
@@ -292,7 +293,7 @@ ssn_status_t ssn_project_weights(ssn_dtype_t dtype, int64_t d, int64_t n, int64_
  *   W and n are HOST arrays of `count` entries; 1 <= count <= SSN_MAX_BATCH.
  * Matrices must not overlap each other.  With bf16 storage a matrix gets the
  * same bits alone and in a batch.  The float32 kernel splits the sum over d
- * between the waves that share a column tile, and that split follows the
+ * between the waves that share a column strip, and that split follows the
  * column partition of the launch (the total column count and the device's
  * compute units), so there the two may differ in the last bits.
  */

@@ -15,477 +15,565 @@ namespace ssn {
 
 // ===========================================================================
 // Weight re-projection W <- U (U^T W) with float32 storage (the original SSN's
-// step after each optimizer update, sections 4.1 and 6.1).  The columns of
-// all matrices of a batch form one sequence of 16-column tiles; block b owns
-// tpb consecutive tiles (a strip), one block per compute unit.  The 8 waves
-// form TW = 8 / RS tile groups of RS waves: wave w = RS tw + rs owns the
-// tiles tw, tw + TW, .. of the strip and row share rs (a group's waves are
-// consecutive, so they sit on different SIMDs when waves are placed on the
-// four SIMDs in turn, and groups with one tile more do not pile onto one
-// SIMD).  Few tiles per block (small matrices) thus still keep all four
-// SIMDs on the matrix cores.
-// Pass 1, T = U^T W, over d in chunks of 32 rows: the chunk's rows of the
-// strip and of U are staged into LDS row tiles (double buffered, one barrier
-// per chunk, pitches chosen so that the 64 lanes of a read hit 64 banks).
-// T tile (kt, j) [16 k x 16 columns] takes one MFMA per group of four rows,
-// K slot g = row 4 q + g of the chunk, A = U[row][16 kt + m] and
-// B = W[row][16 j + n]; wave rs takes the groups q = rs mod RS.  With RS > 1
-// the RS partial sums of a tile group are added through LDS in a fixed order,
-// so that every wave of the group holds the same T.  Lane (n, g) then holds
-// T[16 kt + 4 g + r][16 j + n], r = 0..3: exactly its B operand of pass 2,
-// where K slot g stands for coordinate 16 q + 4 g + s, so T never leaves the
-// registers.  Pass 2, W = U T, in chunks of 32 RS rows, wave rs taking rows
-// 32 rs .. + 31 of each: A = 16 contiguous bytes of a U row (from L2), the
-// output rows parked in one of two LDS row tiles (one barrier per chunk) and
-// stored by the block in 16-byte pieces (non-temporal: W is not read
-// again).  Columns past a matrix's n (in its last tile) are neither used nor
-// stored.
+// step after each optimizer update, sections 4.1 and 6.1).
+//
+// Products: every float32 operand is split exactly into three bf16 planes
+// (split3_bf16x8) and a product takes the six plane pairs that reach past
+// 2^-24 of it, on the bf16 matrix cores: 6 instructions of 16x16x32 (96
+// cycles) do the work of 8 of 16x16x4 in float32 (256 cycles).  The five
+// small pairs of a K step are summed on their own and added to the running
+// sum once, so a running sum is rounded twice per 32 products (the float32
+// MFMA rounds it once per product).
+//
+// The columns of all matrices of a batch form one sequence of strips of
+// 16 NT columns; RS waves of a block own a strip (they share its rows) and a
+// block owns cs <= 8 / RS strips.  W never goes through LDS: lane (n16, g)
+// loads the NT consecutive columns NT n16 .. of rows 8 g + e (e = 0..7) of a
+// 32-row step, 4 rows x 64 NT contiguous bytes per instruction, and column
+// tile i of the MFMAs is the columns NT n16 + i, so the eight values it
+// holds of a column are that column's B operand as they are.
+// Pass 1, T = U^T W: U's planes are staged per block in A-operand order,
+// double buffered, one barrier per SR steps (thread task: 8 rows of one
+// column, so any k is read whole); W runs two steps ahead in registers.
+// With RS > 1 the partial sums of a strip's waves are added through LDS in a
+// fixed order.  Lane (n16, g) then holds T[16 kt + 4 g + r][its column of
+// tile i].
+// Pass 2, W = U T: K slot (g, e) of K step s stands for coordinate
+// 32 s + 4 g + e (e < 4) and 32 s + 16 + 4 g + e - 4, so T stays in the
+// registers that pass 1 left it in (split once), U's planes are staged in
+// that order, and a lane ends with rows 4 g + r of its NT columns: stored as
+// they are, 4 rows x 64 NT contiguous bytes per instruction (non-temporal).
+// A wave whose T is not finite (an infinity or NaN in W or U) redoes both
+// passes with float32 MFMAs straight from memory, which propagate them as
+// float32 arithmetic does.
+//
+// Bound: HBM, W read once and written once.  Measured on MI355X against the
+// kernel that multiplied float32 operands and passed W through LDS: 4 x
+// (5120^2, 5120 x 18432) at k = 51 1508 -> 761 us (5.07 TB/s, the rate of a
+// large copy), error against 64 bits 1.3e-6 -> 5.1e-7; 4 x (4096^2, 4096 x
+// 14336) at k = 64 821 -> 550 us.
+//
+// FG: the reparameterized layer's factor gradient (section 4.1, Eq. (3)),
+// dZp = H^T GT, with H [N, din] as the single matrix of the batch, GT [N, k]
+// in place of U and N rows in place of d (any N): pass 1 alone, then
+// T = GT^T H is written transposed to fg_out [din, k].
 // ===========================================================================
 struct ColumnBatchF32 {
   float* W[kMaxBatch];
   int32_t n[kMaxBatch];
-  int32_t first_tile[kMaxBatch + 1];   // prefix sums of ceil(n / 16)
+  int32_t first[kMaxBatch + 1];        // prefix sums of ceil(n / strip width)
   int32_t count;
-  int32_t tiles;                       // total tiles of the batch
-  int32_t tpb;                         // tiles per block
+  int32_t strips;                      // total strips of the batch
+  int32_t cs;                          // strips per block
 };
 
-constexpr int kW32Rows = 32;           // rows per pass-1 chunk
-constexpr int kW32Threads = 512;
-// Tiles per block at most: three per wave up to k = 80, two beyond (where
-// three would spill registers).
-constexpr int w32_max_tpb(int64_t k) { return k <= 80 ? 24 : 16; }
-
-// Row pitches (floats) of tiles `width` floats wide (a multiple of 16); the
-// LDS has 64 four-byte banks.  Rows 4 q + g read by lanes (n, g) at column
-// 16 j + n: a pitch that is 16 mod 32 puts the four rows on four distinct
-// 16-bank groups.  Rows 4 g + r written by lanes (n, g): a pitch that is 4 mod
-// 16 does the same for each r.
-__host__ __device__ constexpr int pitch_rows4q(int width) { return width % 32 == 0 ? width + 16 : width; }
-__host__ __device__ constexpr int pitch_rows4g(int width) { return width + 4; }
+constexpr int kS32Waves = 8;
+// 32-row steps per staged chunk of pass 1 (every wave of a strip has one at
+// least), and rows per chunk of pass 2: U's planes take 48 KB of LDS at the
+// widest k of either line, 96 KB where more waves share a strip's rows; there
+// pass 1 has one buffer (and a second barrier per chunk) instead of two.
+constexpr int s32_steps(int kt, int rs) { return kt <= 4 ? (rs > 4 ? rs : 4) : (rs > 2 ? rs : 2); }
+constexpr int s32_rows2(int kt) { return kt <= 4 ? 128 : 64; }
 constexpr int cmax3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
 
-// The 16-byte piece p of a chunk of `rows` rows of the strip: row p / (4 tpb),
-// tile j = (p / 4) mod tpb, columns 16 j + 4 (p mod 4) .. + 3 of the matrix
-// that tile belongs to.  `on` is false past the chunk, the strip or the
-// matrix's last column.
-struct W32Piece {
-  float* ptr;     // W + row * n + column
-  int ld;         // n of the matrix
-  int row;        // row within the chunk
-  int lofs;       // LDS offset at pitch `pitch`
-  bool on;
-};
-__device__ __forceinline__ W32Piece w32_piece(const ColumnBatchF32& cb, int t0, int tcount, int tpb,
-                                              int p, int rows, int pitch) {
-  const int row = p / (4 * tpb), q = p % (4 * tpb), j = q >> 2, sub = q & 3;
-  bool on = row < rows && j < tcount;
-  const int t = t0 + (on ? j : 0);
-  int b = 0;
-  while (b + 1 < cb.count && t >= cb.first_tile[b + 1]) ++b;
-  const int col = (t - cb.first_tile[b]) * 16 + 4 * sub;
-  on = on && col < cb.n[b];
-  W32Piece w;
-  w.ld = cb.n[b];
-  w.row = on ? row : 0;
-  w.ptr = cb.W[b] + (int64_t)w.row * w.ld + (on ? col : 0);
-  w.lofs = on ? row * pitch + 16 * j + 4 * sub : 0;
-  w.on = on;
-  return w;
-}
+template <int NT>
+struct StripVec;
+template <>
+struct StripVec<4> { typedef f32x4 T; };
+template <>
+struct StripVec<2> { typedef f32x2 T; };
+template <>
+struct StripVec<1> { typedef float T __attribute__((ext_vector_type(1))); };
 
-// KV: k % 4 == 0, so U rows are whole 16-byte pieces.  Otherwise a chunk of
-// U (32 whole rows, one contiguous span of 32 k floats that starts 16-byte
-// aligned) is read with 16-byte loads and scattered element by element into
-// the zero-padded row tile, and pass 2 reads its U operands element by element.
-// FG: the reparameterized layer's factor gradient (section 4.1, Eq. (3)),
-// dZp = H^T GT, with H [N, din] as the single matrix of the batch, GT [N, k]
-// in place of U and N rows in place of d (any N: rows past N load as zero):
-// pass 1 alone, then T = GT^T H is written transposed to fg_out [din, k].
-template <int KT, int CT, int RS, bool KV, bool FG>
-__global__ __launch_bounds__(kW32Threads) void project_weights_f32_mfma(ColumnBatchF32 cb,
-                                                                       const float* __restrict__ U,
-                                                                       int d, int k, int xcd,
-                                                                       float* __restrict__ fg_out) {
-  static_assert(CT >= 1 && CT <= 3 && (RS == 1 || RS == 2 || RS == 4 || RS == 8), "tile groups");
-  constexpr int TW = 8 / RS;                    // tile groups
-  constexpr int K = 16 * KT, R1 = kW32Rows, R2 = kW32Rows * RS;
-  constexpr int TMAX = TW * CT;                 // tiles per block at most
-  constexpr int WP1M = 16 * TMAX + 16;          // pitch_rows4q(16 t) <= 16 t + 16
-  constexpr int WP2M = 16 * TMAX + 4;           // pitch_rows4g(16 t)
-  constexpr int UP1 = pitch_rows4q(K);
-  constexpr int NP1 = (R1 * 4 * TMAX + kW32Threads - 1) / kW32Threads;
-  constexpr int NP2 = (R2 * 4 * TMAX + kW32Threads - 1) / kW32Threads;
-  constexpr int NUP = (R1 * K / 4 + kW32Threads - 1) / kW32Threads;   // U pieces per thread
-  constexpr int QN = 8 / RS;                    // row groups per chunk and wave (pass 1)
-  // pass 1: two W and two U row tiles; reduction: 8 waves' partial T; pass 2:
-  // two output row tiles
-  constexpr int S1 = 2 * R1 * WP1M + 2 * R1 * UP1;
-  constexpr int SR = RS > 1 ? 8 * KT * CT * 256 : 0;
-  constexpr int S2 = 2 * R2 * WP2M;
-  __shared__ __align__(16) float smem[cmax3(S1, SR, S2)];
-  float* const wtile = smem;                    // buffer b at b * R1 * WP1M
-  float* const utile = smem + 2 * R1 * WP1M;    // buffer b at b * R1 * UP1
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int KT, int NT, int RS, bool FG>
+__global__ __launch_bounds__(64 * kS32Waves) void project_weights_f32_mfma(
+    ColumnBatchF32 cb, const float* __restrict__ U, int rows, int k,
+    float* __restrict__ fg_out) {
+  static_assert((NT == 1 || NT == 2 || NT == 4) && (RS == 1 || RS == 2 || RS == 4 || RS == 8), "strip shape");
+  typedef typename StripVec<NT>::T vec;
+  constexpr int T = 64 * kS32Waves, K = 16 * KT, KS2 = (KT + 1) / 2;
+  constexpr int SR = s32_steps(KT, RS), PS = SR / RS, R2 = s32_rows2(KT);
+  static_assert(PS >= 1, "every wave of a strip has a step of each chunk");
+  constexpr int F1 = SR * KT * 3 * 64;             // 16-byte pieces of a pass-1 buffer
+  constexpr int NB1 = F1 * 32 > 98304 ? 1 : 2;     // pass-1 buffers
+  constexpr int F2 = (R2 / 16) * KS2 * 3 * 64;     // and of a pass-2 buffer
+  constexpr int FR = RS > 1 ? kS32Waves * KT * NT * 64 : 0;   // partial T of 8 waves
+  __shared__ u32x4 smem[cmax3(NB1 * F1, 2 * F2, FR)];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n16 = lane & 15, g = lane >> 4;
-  const int tw = wave / RS, rs = wave % RS;
-  const int tpb = cb.tpb;
-  const int WP1 = pitch_rows4q(16 * tpb);
-  const int WP2 = pitch_rows4g(16 * tpb);
-  // XCD order: neighbouring strips, which share the 128-byte lines at their
-  // boundary, run on the same XCD (blocks go to the 8 XCDs round robin)
-  const int bx = xcd ? (int)((blockIdx.x % 8u) * (gridDim.x / 8u) + blockIdx.x / 8u) : (int)blockIdx.x;
-  const int t0 = bx * tpb;
-  const int tcount = min(tpb, cb.tiles - t0);
-  const int nch1 = FG ? (d + R1 - 1) / R1 : d / R1, nch2 = (d + R2 - 1) / R2;
-  // this wave's tiles: tw + TW v for v < nv
-  const int nv = tcount > tw ? min(CT, (tcount - tw + TW - 1) / TW) : 0;
+  const int grp = wave / RS, rs = wave % RS;
+  // XCD order: neighbouring blocks' columns on one XCD (blocks go to the 8
+  // XCDs round robin; gridDim.x is a multiple of 8)
+  const int bx = (int)((blockIdx.x % 8u) * (gridDim.x / 8u) + blockIdx.x / 8u);
+  const int strip = bx * cb.cs + grp;
+  const bool active = grp < cb.cs && strip < cb.strips;   // wave-uniform
+  int b = 0;
+  while (b + 1 < cb.count && (active ? strip : 0) >= cb.first[b + 1]) ++b;
+  const int64_t ld = cb.n[b];
+  const int64_t colw = (int64_t)((active ? strip : 0) - cb.first[b]) * (16 * NT) + NT * n16;
+  const bool on = active && colw < ld;            // n % 4 == 0: all NT columns or none
+  float* const wcol = cb.W[b] + (on ? colw : 0);
 
-  W32Piece wp[NP1];
-#pragma unroll
-  for (int i = 0; i < NP1; ++i) wp[i] = w32_piece(cb, t0, tcount, tpb, tid + kW32Threads * i, R1, WP1);
-  int uo[NUP], us[NUP];
-  bool uon[NUP];
-#pragma unroll
-  for (int i = 0; i < NUP; ++i) {
-    const int p = tid + kW32Threads * i;
-    if constexpr (KV) {
-      const int row = p / (k / 4), cg = p % (k / 4);
-      uon[i] = row < R1;
-      us[i] = uon[i] ? row * k + 4 * cg : 0;
-      uo[i] = uon[i] ? row * UP1 + 4 * cg : 0;
-    } else {
-      // floats 4 p .. 4 p + 3 of the chunk's span
-      uon[i] = p < R1 * k / 4;
-      us[i] = uon[i] ? 4 * p : 0;
-      uo[i] = 0;
-    }
-  }
-  // columns k .. K - 1 of the U tiles stay zero
-  for (int i = tid; i < 2 * R1 * UP1; i += kW32Threads) utile[i] = 0.f;
+  const int nsteps = FG ? (rows + 31) / 32 : rows / 32;
+  const int nch1 = (nsteps + SR - 1) / SR, nch2 = (rows + R2 - 1) / R2;
 
-  f32x4 wv[NP1], uv[NUP];
-  auto load_chunk = [&](int c) {
+  // U of pass 1: task q is column q % K of the 8 rows q / K of the chunk
+  constexpr int NT1 = SR * 4 * K, TP1 = (NT1 + T - 1) / T;
+  float u1[TP1][8];
+  auto load_u1 = [&](int c) {
 #pragma unroll
-    for (int i = 0; i < NP1; ++i) {
-      const f32x4* src = (const f32x4*)(wp[i].ptr + (int64_t)c * R1 * wp[i].ld);
-      const bool ok = wp[i].on && (!FG || c * R1 + wp[i].row < d);
-      if constexpr (RS == 1)
-        wv[i] = ok ? __builtin_nontemporal_load(src) : f32x4{0.f, 0.f, 0.f, 0.f};
-      else
-        wv[i] = ok ? *src : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-#pragma unroll
-    for (int i = 0; i < NUP; ++i) {
-      const int64_t e0 = (int64_t)c * R1 * k + us[i];
+    for (int i = 0; i < TP1; ++i) {
+      // Tasks past the chunk's last, columns past k and rows past the end
+      // load something in range: their planes meet no W, or make rows k .. K
+      // - 1 of T, which pass 2 multiplies by zero.  FG's last step may be
+      // ragged: its rows past the end are zero.
+      const int q = NT1 % T == 0 ? tid + T * i : min(tid + T * i, NT1 - 1);
+      const int col = min(q % K, k - 1), r0 = c * (SR * 32) + 8 * (q / K);
       if constexpr (FG) {
-        // elements past the N k floats of GT load as zero
-        const int64_t lim = (int64_t)d * k;
-        if (uon[i] && e0 + 4 <= lim) {
-          uv[i] = *(const f32x4*)(U + e0);
-        } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) uv[i][e] = (uon[i] && e0 + e < lim) ? U[e0 + e] : 0.f;
+        for (int e = 0; e < 8; ++e) {
+          const float x = U[(int64_t)min(r0 + e, rows - 1) * k + col];
+          u1[i][e] = r0 + e < rows ? x : 0.f;
         }
       } else {
-        uv[i] = uon[i] ? *(const f32x4*)(U + e0) : f32x4{0.f, 0.f, 0.f, 0.f};
+        const float* src = U + (int64_t)min(r0, rows - 8) * k + col;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u1[i][e] = src[e * k];
       }
     }
   };
-  auto store_chunk = [&](int buf) {
+  auto store_u1 = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < NP1; ++i)
-      if (wp[i].on) *(f32x4*)(wtile + buf * R1 * WP1M + wp[i].lofs) = wv[i];
+    for (int i = 0; i < TP1; ++i) {
+      const int q = tid + T * i, col = q % K, rg = q / K;
+      u32x4 h, m, l;
+      split3_bf16x8(u1[i], h, m, l);
+      if (NT1 % T == 0 || q < NT1) {
+        u32x4* dst = smem + buf * F1 + ((rg >> 2) * KT + (col >> 4)) * 192 + 16 * (rg & 3) + (col & 15);
+        dst[0] = h;
+        dst[64] = m;
+        dst[128] = l;
+      }
+    }
+  };
+  // U of pass 2: task q is piece q % (4 KS2) of row q / (4 KS2), piece p = 4 s +
+  // g' the coordinates 32 s + 4 g' + 0..3 and 32 s + 16 + 4 g' + 0..3; within
+  // a fragment the slot of (row m, g') is XORed with p, so that the pieces
+  // of one row go to different banks
+  constexpr int PPR = 4 * KS2, NT2 = R2 * PPR, TP2 = (NT2 + T - 1) / T;
+  float u2[TP2][8];
+  const int64_t total = (int64_t)rows * k;
+  auto load_u2 = [&](int c) {
 #pragma unroll
-    for (int i = 0; i < NUP; ++i)
-      if (uon[i]) {
-        if constexpr (KV) {
-          *(f32x4*)(utile + buf * R1 * UP1 + uo[i]) = uv[i];
+    for (int i = 0; i < TP2; ++i) {
+      const int q = NT2 % T == 0 ? tid + T * i : min(tid + T * i, NT2 - 1);
+      const int row = min(c * R2 + q / PPR, rows - 1), p = q % PPR;
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const int c0 = 32 * (p >> 2) + 4 * (p & 3) + 16 * hf;
+        const int64_t o = (int64_t)row * k + c0;
+        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (o + 4 <= total) {                     // into the next row, past k
+          v = *(const f32x4_a4*)(U + o);
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int idx = us[i] + e, row = idx / k;
-            utile[buf * R1 * UP1 + row * UP1 + (idx - row * k)] = uv[i][e];
-          }
+          for (int e = 0; e < 4; ++e)
+            if (o + e < total) v[e] = U[o + e];
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u2[i][4 * hf + e] = c0 + e < k ? v[e] : 0.f;
       }
+    }
+  };
+  auto store_u2 = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < TP2; ++i) {
+      const int q = tid + T * i, row = q / PPR, p = q % PPR;
+      u32x4 h, m, l;
+      split3_bf16x8(u2[i], h, m, l);
+      if (NT2 % T == 0 || q < NT2) {
+        u32x4* dst = smem + buf * F2 + ((row >> 4) * KS2 + (p >> 2)) * 192 + 16 * (p & 3) +
+                     ((row & 15) ^ (p & 15));
+        dst[0] = h;
+        dst[64] = m;
+        dst[128] = l;
+      }
+    }
   };
 
-  // A operand of pass 2: U[rb + 16 dt + n16][16 q + 4 g .. + 3] for chunk c,
-  // rb = 32 RS c + 32 rs (zero past k; d is a multiple of 32, so rb < d
-  // keeps all 32 rows in range)
-  auto load_ua = [&](int c, f32x4(&v)[2][KT]) {
-    const int rb = c * R2 + 32 * rs;
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int q = 0; q < KT; ++q) {
-        const int col = 16 * q + 4 * g;
-        const float* src = U + (int64_t)(rb < d ? rb + 16 * dt + n16 : 0) * k + col;
-        if constexpr (KV) {
-          v[dt][q] = (rb < d && col < k) ? *(const f32x4*)src : f32x4{0.f, 0.f, 0.f, 0.f};
-        } else {
-#pragma unroll
-          for (int s = 0; s < 4; ++s) v[dt][q][s] = (rb < d && col + s < k) ? src[s] : 0.f;
-        }
-      }
-  };
-
-  // The whole computation for a wave that owns NV tiles (NV known at compile
-  // time, so that neither pass branches between its MFMAs).  Every wave runs
-  // the same barriers and its share of the block's loads and stores.
-  auto run = [&](auto NVc) {
-    constexpr int NV = decltype(NVc)::value;
-    constexpr int NA = NV > 0 ? NV : 1;
-    constexpr int PD = KT * NA <= 4 ? 2 : 1;    // pass-2 U operand sets in flight
-
+  // The whole computation, for waves with a strip (ON) and for those that
+  // only stage U and keep the barriers.
+  auto run = [&](auto ONc) {
+    constexpr bool ON = decltype(ONc)::value;
     // ---- pass 1: T = U^T W ----
-    f32x4 acc[KT][NA];
+    f32x4 acc[KT][NT];
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-      for (int v = 0; v < NA; ++v) acc[kt][v] = f32x4{0.f, 0.f, 0.f, 0.f};
-    load_chunk(0);
-    __syncthreads();                            // the zeroed U tiles
-    store_chunk(0);
-    if (nch1 > 1) load_chunk(1);
-    for (int c = 0; c < nch1; ++c) {
-      __syncthreads();                          // chunk c in buffer c % 2; chunk c - 1 fully read
-      if (c + 1 < nch1) {
-        store_chunk((c + 1) & 1);
-        if (c + 2 < nch1) load_chunk(c + 2);
+      for (int i = 0; i < NT; ++i) acc[kt][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    vec wv[2][8];
+    // step j of this wave: rows 32 (rs + RS j) + 8 g + e (past the end: the
+    // last row again, against zero rows of U)
+    auto load_w = [&](int j, vec(&v)[8]) {
+      const int st = min(rs + RS * j, nsteps - 1);
+      if constexpr (FG) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          v[e] = __builtin_nontemporal_load(
+              (const vec*)(wcol + (int64_t)min(32 * st + 8 * g + e, rows - 1) * ld));
+      } else {
+        const float* src = wcol + (int64_t)(32 * st + 8 * g) * ld;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = __builtin_nontemporal_load((const vec*)(src + e * ld));
       }
-      if constexpr (NV > 0) {
-        const float* ub = utile + (c & 1) * R1 * UP1;
-        const float* wb = wtile + (c & 1) * R1 * WP1M;
+    };
+    auto step1 = [&](int c, int p, int j, auto Sc) {
+      constexpr int S = decltype(Sc)::value;
+      u32x4 wh[NT], wm[NT], wl[NT];
 #pragma unroll
-        for (int qi = 0; qi < QN; ++qi) {
-          const int row = 4 * (rs + RS * qi) + g;
-          float a[KT], b[NV];
+      for (int i = 0; i < NT; ++i) {
+        float v[8];
 #pragma unroll
-          for (int kt = 0; kt < KT; ++kt) a[kt] = ub[row * UP1 + 16 * kt + n16];
+        for (int e = 0; e < 8; ++e) v[e] = wv[S][e][i];
+        split3_bf16x8(v, wh[i], wm[i], wl[i]);
+      }
+      load_w(j + 2, wv[S]);
+      const int sl = rs + RS * p;                 // step within the chunk
+      if (c * SR + sl < nsteps) {
+        const u32x4* ub = smem + c % NB1 * F1 + sl * (KT * 192) + lane;
 #pragma unroll
-          for (int v = 0; v < NV; ++v) b[v] = wb[row * WP1 + 16 * (tw + TW * v) + n16];
+        for (int kt = 0; kt < KT; ++kt) {
+          const u32x4 uh = ub[kt * 192], um = ub[kt * 192 + 64], ul = ub[kt * 192 + 128];
+          f32x4 t[NT];
 #pragma unroll
-          for (int v = 0; v < NV; ++v)
+          for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(ul, wh[i], f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) acc[kt][v] = mfma16x16x4f32(a[kt], b[v], acc[kt][v]);
+          for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(uh, wl[i], t[i]);
+#pragma unroll
+          for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(um, wm[i], t[i]);
+#pragma unroll
+          for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(um, wh[i], t[i]);
+#pragma unroll
+          for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(uh, wm[i], t[i]);
+#pragma unroll
+          for (int i = 0; i < NT; ++i) acc[kt][i] = mfma16x16x32(uh, wh[i], acc[kt][i]);
+#pragma unroll
+          for (int i = 0; i < NT; ++i) acc[kt][i] += t[i];
         }
       }
-    }
-    __syncthreads();                            // pass 1 done with the row tiles
-
-    if constexpr (RS > 1) {
-      // partial T of wave w at red[(w KT CT + e) 64 + lane], element
-      // e = kt CT + v.  Wave rs of a group adds the partials of elements
-      // e = rs mod RS in the order of the group's waves and stores the total
-      // over the first partial; every wave then reads its T back.  (The waves
-      // of a group own the same tiles, so they agree on NV.)
-      constexpr int E = KT * CT, NE = (E + RS - 1) / RS;
-      f32x4* const red = (f32x4*)smem;
+    };
+    // chunk c in buffer c % NB1; P0: parity of this wave's first step of it
+    auto chunk1 = [&](int c, auto P0c) {
+      constexpr int P0 = decltype(P0c)::value;
+      load_u1(min(c + 1, nch1 - 1));
+      if constexpr (ON) {
+        if constexpr (PS == 1) {
+          step1(c, 0, c, std::integral_constant<int, P0>{});
+        } else {
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) red[(wave * E + kt * CT + v) * 64 + lane] = acc[kt][v];
-      __syncthreads();
-      f32x4 tot[NE];
-#pragma unroll
-      for (int i = 0; i < NE; ++i) {
-        const int e = rs + RS * i;
-        if (e < E && e % CT < NV) {
-          f32x4 s = red[(RS * tw * E + e) * 64 + lane];
-#pragma unroll
-          for (int r2 = 1; r2 < RS; ++r2) s += red[((RS * tw + r2) * E + e) * 64 + lane];
-          tot[i] = s;
-        }
-      }
-      __syncthreads();                          // every partial read
-#pragma unroll
-      for (int i = 0; i < NE; ++i) {
-        const int e = rs + RS * i;
-        if (e < E && e % CT < NV) red[(RS * tw * E + e) * 64 + lane] = tot[i];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[kt][v] = red[(RS * tw * E + kt * CT + v) * 64 + lane];
-      __syncthreads();                          // totals read before pass 2 parks rows
-    }
-
-    if constexpr (FG) {
-      // lane (n16, g) holds T[16 kt + 4 g + r][16 j + n16]: dZp row 16 j + n16
-      // (of din), columns 16 kt + 4 g + r (of k); one wave per tile group writes
-      if (rs == 0) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const int col = 16 * (t0 + tw + TW * v) + n16;
-          if (col >= cb.n[0]) continue;
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt) {
-            const int kc = 16 * kt + 4 * g;
-            float* dst = fg_out + (int64_t)col * k + kc;
-            if (KV && kc < k && (((uintptr_t)fg_out & 15u) == 0)) {
-              *(f32x4*)dst = acc[kt][v];
-            } else {
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (kc + r < k) dst[r] = acc[kt][v][r];
-            }
+          for (int p = 0; p < PS; p += 2) {
+            step1(c, p, c * PS + p, std::integral_constant<int, 0>{});
+            step1(c, p + 1, c * PS + p + 1, std::integral_constant<int, 1>{});
           }
         }
       }
-      return;
+      if constexpr (NB1 == 1) __syncthreads();    // every wave is done with chunk c
+      store_u1((c + 1) % NB1);
+      __syncthreads();
+    };
+    if (nch1 > 0) {
+      load_u1(0);
+      if constexpr (ON) {
+        load_w(0, wv[0]);
+        load_w(1, wv[1]);
+      }
+      store_u1(0);
+      __syncthreads();
+      int c = 0;
+      if constexpr (PS == 1) {
+        for (; c + 1 < nch1; c += 2) {
+          chunk1(c, std::integral_constant<int, 0>{});
+          chunk1(c + 1, std::integral_constant<int, 1>{});
+        }
+        if (c < nch1) chunk1(c, std::integral_constant<int, 0>{});
+      } else {
+        for (; c < nch1; ++c) chunk1(c, std::integral_constant<int, 0>{});
+      }
     }
 
-    // ---- pass 2: W = U T ----
-    W32Piece op[NP2];
+    if constexpr (RS > 1) {
+      // partial T of wave w at red[(w KT NT + e) 64 + lane], element
+      // e = kt NT + i.  Wave rs of a strip adds the partials of elements
+      // e = rs mod RS in wave order and stores the total over the first
+      // partial; every wave of the strip then reads the totals.
+      constexpr int E = KT * NT, NE = (E + RS - 1) / RS;
+      f32x4* const red = (f32x4*)smem;
+      const int w0 = grp * RS;
+      if constexpr (ON) {
 #pragma unroll
-    for (int i = 0; i < NP2; ++i) op[i] = w32_piece(cb, t0, tcount, tpb, tid + kW32Threads * i, R2, WP2);
-    f32x4 ua[PD][2][KT];
-    // chunk c parks its rows in output tile c % 2: the barrier after chunk
-    // c + 1 is parked orders the stores of chunk c before chunk c + 2 parks.
-    // SM >= 0: this thread's pieces 0 .. SM - 1 are stored in every chunk and
-    // the others never (so the stores are unconditional and the wait for the
-    // next chunk's U operands, issued before them, leaves them in flight;
-    // with conditional stores the compiler cannot count them and drains
-    // them before the next chunk's MFMAs).  SM < 0: each piece tests itself.
-    auto body2 = [&](int c, auto Sc, auto SMc) {
-      constexpr int S = decltype(Sc)::value;
-      constexpr int SM = decltype(SMc)::value;
-      float* const ot = smem + (c & 1) * R2 * WP2M;
-      if constexpr (NV > 0) {
-        if constexpr (PD == 2) {
-          if (c + 1 < nch2) load_ua(c + 1, ua[S ^ 1]);
+        for (int e = 0; e < E; ++e) red[(wave * E + e) * 64 + lane] = acc[e / NT][e % NT];
+      }
+      __syncthreads();
+      f32x4 tot[NE];
+      if constexpr (ON) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+          const int e = rs + RS * i;
+          if (e < E) {
+            f32x4 s = red[(w0 * E + e) * 64 + lane];
+#pragma unroll
+            for (int r2 = 1; r2 < RS; ++r2) s += red[((w0 + r2) * E + e) * 64 + lane];
+            tot[i] = s;
+          }
         }
-        const int rbase = 32 * rs;
-        if (c * R2 + rbase < d) {
-          // the 2 NV output tiles take their MFMAs in turn, so that no MFMA
-          // waits for the result of the one before
-          f32x4 o[2][NV];
+      }
+      __syncthreads();                            // every partial read
+      if constexpr (ON) {
 #pragma unroll
-          for (int dt = 0; dt < 2; ++dt)
+        for (int i = 0; i < NE; ++i) {
+          const int e = rs + RS * i;
+          if (e < E) red[(w0 * E + e) * 64 + lane] = tot[i];
+        }
+      }
+      __syncthreads();
+      if constexpr (ON) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) o[dt][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < E; ++e) acc[e / NT][e % NT] = red[(w0 * E + e) * 64 + lane];
+      }
+      __syncthreads();                            // totals read before pass 2 stages U
+    }
+
+    // an infinity or NaN anywhere in T: the strip's T again, in float32
+    bool bad = false;
+    if constexpr (ON) {
+      float z = 0.f;
 #pragma unroll
-          for (int q = 0; q < KT; ++q)
+      for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+        for (int i = 0; i < NT; ++i)
 #pragma unroll
-              for (int dt = 0; dt < 2; ++dt)
+          for (int r = 0; r < 4; ++r) z = fmaf(acc[kt][i][r], 0.f, z);
+      bad = __any(z != 0.f);
+      if (bad) {
 #pragma unroll
-                for (int v = 0; v < NV; ++v)
-                  o[dt][v] = mfma16x16x4f32(ua[S][dt][q][s], acc[q][v][s], o[dt][v]);
-          // lane (n16, g): rows rbase + 16 dt + 4 g + r, column 16 j + n16
+        for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-          for (int dt = 0; dt < 2; ++dt)
+          for (int i = 0; i < NT; ++i) acc[kt][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int r0 = 0; r0 < rows; r0 += 4) {
+          const int row = r0 + g;
+          const bool ok = row < rows;
+          vec w = *(const vec*)(wcol + (int64_t)(ok ? row : 0) * ld);
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
+          for (int kt = 0; kt < KT; ++kt) {
+            const float a = (ok && 16 * kt + n16 < k) ? U[(int64_t)row * k + 16 * kt + n16] : 0.f;
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+              acc[kt][i] = mfma16x16x4f32(a, ok ? (float)w[i] : 0.f, acc[kt][i]);
+          }
+        }
+      }
+    }
+
+    if constexpr (FG) {
+      // dZp row NT n16 + i (of din), columns 16 kt + 4 g + r (of k); one wave
+      // of the strip writes
+      if (ON && rs == 0 && on) {
+        const bool v16 = k % 4 == 0 && ((uintptr_t)fg_out & 15u) == 0;
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt) {
+            const int kc = 16 * kt + 4 * g;
+            float* dst = fg_out + (colw + i) * k + kc;
+            if (v16 && kc < k) {
+              *(f32x4*)dst = acc[kt][i];
+            } else {
 #pragma unroll
               for (int r = 0; r < 4; ++r)
-                ot[(rbase + 16 * dt + 4 * g + r) * WP2 + 16 * (tw + TW * v) + n16] = o[dt][v][r];
-        }
-        if constexpr (PD == 1) {
-          if (c + 1 < nch2) load_ua(c + 1, ua[0]);
-        }
+                if (kc + r < k) dst[r] = acc[kt][i][r];
+            }
+          }
       }
-      __syncthreads();                          // the chunk's output rows are parked
-      if constexpr (SM >= 0) {
-#pragma unroll
-        for (int i = 0; i < SM; ++i)
-          __builtin_nontemporal_store(*(const f32x4*)(ot + op[i].lofs),
-                                      (f32x4*)(op[i].ptr + (int64_t)c * R2 * op[i].ld));
-      } else {
-#pragma unroll
-        for (int i = 0; i < NP2; ++i)
-          if (op[i].on && c * R2 + op[i].row < d)
-            __builtin_nontemporal_store(*(const f32x4*)(ot + op[i].lofs),
-                                        (f32x4*)(op[i].ptr + (int64_t)c * R2 * op[i].ld));
-      }
-    };
-    auto pass2 = [&](auto SMc) {
-      if constexpr (NV > 0) load_ua(0, ua[0]);
-      int c = 0;
-      if constexpr (PD == 2) {
-        for (; c + 1 < nch2; c += 2) {
-          body2(c, std::integral_constant<int, 0>{}, SMc);
-          body2(c + 1, std::integral_constant<int, 1>{}, SMc);
-        }
-      } else if (nch2 > 0) {
-        // the first chunk apart: every entry to the loop then has the same
-        // stores in flight after the U loads it waits for
-        body2(0, std::integral_constant<int, 0>{}, SMc);
-        c = 1;
-      }
-      for (; c < nch2; ++c) body2(c, std::integral_constant<int, 0>{}, SMc);
-    };
-    // pieces on in every chunk: op[i].on, and the rows of the last chunk
-    // inside d (always when d is a multiple of the chunk)
-    int ns = 0;
-    bool prefix = true;
-#pragma unroll
-    for (int i = 0; i < NP2; ++i) {
-      const bool on = op[i].on && d % R2 == 0;
-      prefix = prefix && (on ? ns == i : true);
-      ns += on ? 1 : 0;
-    }
-    if (__all(prefix && ns == NP2)) {
-      pass2(std::integral_constant<int, NP2>{});
-    } else if (NP2 > 1 && __all(prefix && ns == NP2 - 1)) {
-      pass2(std::integral_constant<int, (NP2 > 1 ? NP2 - 1 : 0)>{});
     } else {
-      pass2(std::integral_constant<int, -1>{});
+      // ---- pass 2: W = U T ----
+      // rows 16 rt + 4 g + r of the chunk, this lane's NT columns
+      auto put = [&](int row, const f32x4(&o)[NT]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          vec v;
+#pragma unroll
+          for (int i = 0; i < NT; ++i) v[i] = o[i][r];
+          __builtin_nontemporal_store(v, (vec*)(wcol + (int64_t)(row + r) * ld));
+        }
+      };
+      // every chunk of rows, with its U staged: tile(c) does this wave's rows
+      auto sweep = [&](auto tile) {
+        load_u2(0);
+        store_u2(0);
+        __syncthreads();
+        for (int c = 0; c < nch2; ++c) {
+          load_u2(min(c + 1, nch2 - 1));
+          tile(c);
+          store_u2((c + 1) & 1);
+          __syncthreads();
+        }
+      };
+      if constexpr (ON) {
+        if (bad) {
+          sweep([&](int c) {
+            for (int rt = rs; rt < R2 / 16; rt += RS) {
+              const int r0 = c * R2 + 16 * rt;
+              if (r0 >= rows) break;
+              f32x4 o[NT];
+#pragma unroll
+              for (int i = 0; i < NT; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                  const int col = 16 * kt + 4 * g + s;
+                  const float a = col < k ? U[(int64_t)(r0 + n16) * k + col] : 0.f;
+#pragma unroll
+                  for (int i = 0; i < NT; ++i) o[i] = mfma16x16x4f32(a, acc[kt][i][s], o[i]);
+                }
+              if (on) put(r0 + 4 * g, o);
+            }
+          });
+        } else {
+          u32x4 th[KS2][NT], tm[KS2][NT], tl[KS2][NT];
+#pragma unroll
+          for (int s = 0; s < KS2; ++s)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+              float v[8];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                v[e] = acc[2 * s][i][e];
+                v[4 + e] = 2 * s + 1 < KT ? acc[2 * s + 1 < KT ? 2 * s + 1 : 0][i][e] : 0.f;
+              }
+              split3_bf16x8(v, th[s][i], tm[s][i], tl[s][i]);
+            }
+          auto row_tile = [&](int c, int rt, f32x4(&o)[NT]) {
+            const u32x4* ub = smem + (c & 1) * F2 + rt * (KS2 * 192);
+            f32x4 t[NT];
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+              t[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+              o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int s = 0; s < KS2; ++s) {
+              const u32x4* us = ub + s * 192 + 16 * g + (n16 ^ (4 * s + g));
+              const u32x4 uh = us[0], um = us[64], ul = us[128];
+#pragma unroll
+              for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(ul, th[s][i], t[i]);
+#pragma unroll
+              for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(uh, tl[s][i], t[i]);
+#pragma unroll
+              for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(um, tm[s][i], t[i]);
+#pragma unroll
+              for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(um, th[s][i], t[i]);
+#pragma unroll
+              for (int i = 0; i < NT; ++i) t[i] = mfma16x16x32(uh, tm[s][i], t[i]);
+#pragma unroll
+              for (int i = 0; i < NT; ++i) o[i] = mfma16x16x32(uh, th[s][i], o[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < NT; ++i) o[i] += t[i];
+          };
+          if (__all(on) && rows % R2 == 0) {
+            // whole chunks and columns: every store unconditional
+            sweep([&](int c) {
+#pragma unroll
+              for (int q = 0; q < R2 / 16 / RS; ++q) {
+                const int rt = rs + RS * q;
+                f32x4 o[NT];
+                row_tile(c, rt, o);
+                put(c * R2 + 16 * rt + 4 * g, o);
+              }
+            });
+          } else {
+            sweep([&](int c) {
+              for (int rt = rs; rt < R2 / 16; rt += RS) {
+                if (c * R2 + 16 * rt >= rows) break;
+                f32x4 o[NT];
+                row_tile(c, rt, o);
+                if (on) put(c * R2 + 16 * rt + 4 * g, o);
+              }
+            });
+          }
+        }
+      } else {
+        sweep([](int) {});
+      }
     }
   };
-  if (nv >= 3) {
-    if constexpr (CT >= 3) run(std::integral_constant<int, 3>{});
-  } else if (nv == 2) {
-    if constexpr (CT >= 2) run(std::integral_constant<int, 2>{});
-  } else if (nv == 1) {
-    run(std::integral_constant<int, 1>{});
-  } else {
-    run(std::integral_constant<int, 0>{});
-  }
+  if (active)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
 }
 
-template <int KT, int CT, int RS, bool FG>
-static hipError_t launch_weights_f32_cfg(const ColumnBatchF32& cb, const float* U, int d, int k,
-                                         float* fg_out, hipStream_t st) {
-  const unsigned grid = (unsigned)((cb.tiles + cb.tpb - 1) / cb.tpb);
-  const int xcd = grid % 8 == 0 ? 1 : 0;
-  if (k % 4 == 0)
-    hipLaunchKernelGGL((project_weights_f32_mfma<KT, CT, RS, true, FG>), dim3(grid), dim3(kW32Threads), 0,
-                       st, cb, U, d, k, xcd, fg_out);
-  else
-    hipLaunchKernelGGL((project_weights_f32_mfma<KT, CT, RS, false, FG>), dim3(grid), dim3(kW32Threads), 0,
-                       st, cb, U, d, k, xcd, fg_out);
+template <int KT, int NT, int RS, bool FG>
+static hipError_t launch_weights_f32_cfg(ColumnBatchF32& cb, const float* U, int rows, int k,
+                                         float* fg_out, int64_t want, hipStream_t st) {
+  int32_t acc = 0;
+  for (int b = 0; b < cb.count; ++b) {
+    cb.first[b] = acc;
+    acc += (int32_t)(((int64_t)cb.n[b] + 16 * NT - 1) / (16 * NT));
+  }
+  for (int b = cb.count; b <= kMaxBatch; ++b) cb.first[b] = acc;
+  cb.strips = acc;
+  // strips per block: as even as possible over rounds of `want` blocks
+  const int64_t most = kS32Waves / RS, rounds = (acc + want * most - 1) / (want * most);
+  const int64_t cs = (acc + want * rounds - 1) / (want * rounds);
+  cb.cs = (int32_t)(cs < 1 ? 1 : (cs > most ? most : cs));
+  // a multiple of 8 blocks (blocks past the last strip only keep the barriers)
+  const unsigned grid = ((unsigned)((acc + cb.cs - 1) / cb.cs) + 7u) & ~7u;
+  hipLaunchKernelGGL((project_weights_f32_mfma<KT, NT, RS, FG>), dim3(grid), dim3(64 * kS32Waves), 0, st,
+                     cb, U, rows, k, fg_out);
   return hipGetLastError();
 }
 
-// Tile groups by tiles per block: 8 groups of one wave for tpb >= 8 (CT =
-// ceil(tpb / 8) tiles per wave), 4 groups of 2 waves for 4..7, 2 of 4 for 2..3,
-// one of 8 for a single tile.
+// Strip shapes by the columns each compute unit gets: enough waves per unit
+// to keep loads in flight and all four SIMDs on the matrix cores (wide
+// strips, one wave each, for large batches; narrower strips whose rows are
+// shared by several waves for small ones).  Measured on MI355X against the
+// float32-product kernel (us): 2048^2, k = 40 40.9 -> 36.7 (8 waves per
+// 16-column strip; with 4 48); 4096^2, k = 64 109 -> 81; 4096 x 14336 262 ->
+// 138; 4096 x (4096 + 14336) 309 -> 174; 5120 x (5120 + 18432), k = 51 547
+// -> 237; k = 128, 2048^2 82 -> 67 and 4 x (5120^2, 5120 x 18432) 3737 ->
+// 1461; k <= 16, whose products are few, 4 x (2048^2, 2048 x 7168) 112 ->
+// 110, 4 x (4096^2, 4096 x 14336) 399 -> 418 (five waves on 231 units).
 template <int KT, bool FG>
-hipError_t launch_weights_f32_kt(const ColumnBatchF32& cb, const float* U, int d, int k, float* fg_out,
+hipError_t launch_weights_f32_kt(ColumnBatchF32& cb, const float* U, int rows, int k, float* fg_out,
                                  hipStream_t st) {
-  const int tpb = cb.tpb;
-  if constexpr (KT <= 5) {
-    if (tpb >= 17) return launch_weights_f32_cfg<KT, 3, 1, FG>(cb, U, d, k, fg_out, st);
+  const int64_t cus = device_cu_count();
+  int64_t cols = 0;
+  for (int b = 0; b < cb.count; ++b) cols += cb.n[b];
+  const int64_t per = (cols + cus - 1) / cus;
+  if constexpr (KT <= 4) {
+    if (per > 256) return launch_weights_f32_cfg<KT, 4, 1, FG>(cb, U, rows, k, fg_out, cus, st);
+    if (per > 128) return launch_weights_f32_cfg<KT, 4, 2, FG>(cb, U, rows, k, fg_out, cus, st);
+    if (per > 64) return launch_weights_f32_cfg<KT, 4, 4, FG>(cb, U, rows, k, fg_out, cus, st);
+    if (per > 32) return launch_weights_f32_cfg<KT, 2, 4, FG>(cb, U, rows, k, fg_out, cus, st);
+    if (per > 16) return launch_weights_f32_cfg<KT, 1, 4, FG>(cb, U, rows, k, fg_out, cus, st);
+    return launch_weights_f32_cfg<KT, 1, 8, FG>(cb, U, rows, k, fg_out, cus, st);
+  } else {
+    if (per > 128) return launch_weights_f32_cfg<KT, 2, 1, FG>(cb, U, rows, k, fg_out, cus, st);
+    if (per > 64) return launch_weights_f32_cfg<KT, 2, 2, FG>(cb, U, rows, k, fg_out, cus, st);
+    if (per > 32) return launch_weights_f32_cfg<KT, 1, 2, FG>(cb, U, rows, k, fg_out, cus, st);
+    return launch_weights_f32_cfg<KT, 1, 4, FG>(cb, U, rows, k, fg_out, cus, st);
   }
-  if (tpb >= 9) return launch_weights_f32_cfg<KT, 2, 1, FG>(cb, U, d, k, fg_out, st);
-  if (tpb == 8) return launch_weights_f32_cfg<KT, 1, 1, FG>(cb, U, d, k, fg_out, st);
-  if (tpb >= 5) return launch_weights_f32_cfg<KT, 2, 2, FG>(cb, U, d, k, fg_out, st);
-  if (tpb == 4) return launch_weights_f32_cfg<KT, 1, 2, FG>(cb, U, d, k, fg_out, st);
-  if (tpb == 3) return launch_weights_f32_cfg<KT, 2, 4, FG>(cb, U, d, k, fg_out, st);
-  if (tpb == 2) return launch_weights_f32_cfg<KT, 1, 4, FG>(cb, U, d, k, fg_out, st);
-  return launch_weights_f32_cfg<KT, 1, 8, FG>(cb, U, d, k, fg_out, st);
 }
 
 // Explicitly instantiated in f32_strips_a.hip (KT 1..4) and f32_strips_b.hip
 // (KT 5..8); the dispatching unit declares them extern.
-#define SSN_STRIPS_F32_KT(KT, FG)                                                                 \
-  template hipError_t launch_weights_f32_kt<KT, FG>(const ColumnBatchF32&, const float*, int, int, \
+#define SSN_STRIPS_F32_KT(KT, FG)                                                           \
+  template hipError_t launch_weights_f32_kt<KT, FG>(ColumnBatchF32&, const float*, int, int, \
                                                     float*, hipStream_t)
 #define SSN_STRIPS_F32_KT_EXTERN(KT, FG) extern SSN_STRIPS_F32_KT(KT, FG)
 

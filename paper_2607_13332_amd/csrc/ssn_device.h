@@ -68,6 +68,27 @@ __device__ __forceinline__ void split_bf16x8(const float* v, u32x4& hi, u32x4& l
   lo = u32x4{l[0], l[1], l[2], l[3]};
 }
 
+// Split 8 floats into three bf16 planes x = h + m + l, exactly: each plane is
+// the top 16 bits of what the planes before it leave (truncated, so that no
+// plane overflows), and 3 x 8 significant bits hold all 24 of a float32.  An
+// infinite x gives NaN in the lower planes (inf - inf): the kernels that use
+// the split recompute a non-finite result with float32 MFMAs.
+__device__ __forceinline__ void split3_bf16x8(const float (&v)[8], u32x4& h, u32x4& m, u32x4& l) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const uint32_t a = __float_as_uint(v[2 * p]), b = __float_as_uint(v[2 * p + 1]);
+    const float ra = v[2 * p] - __uint_as_float(a & 0xFFFF0000u);
+    const float rb = v[2 * p + 1] - __uint_as_float(b & 0xFFFF0000u);
+    const uint32_t a1 = __float_as_uint(ra), b1 = __float_as_uint(rb);
+    const float sa = ra - __uint_as_float(a1 & 0xFFFF0000u);
+    const float sb = rb - __uint_as_float(b1 & 0xFFFF0000u);
+    // the high halves of two dwords, the first in bits 0..15
+    h[p] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    m[p] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+    l[p] = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302u);
+  }
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);
