@@ -174,7 +174,7 @@ def traffic_op(kernel_name: str, grid: int):
     a = _template_args(kernel_name)
     if "copyBuffer" in kernel_name:
         return "calibration"
-    if "decompress_mfma_bf16" in kernel_name and a[:1] == ["2"]:
+    if any(n in kernel_name for n in ("decompress_cols_bf16", "decompress_mfma_bf16")) and a[:1] == ["2"]:
         return "decompress" if a[1] == "true" else "expand_grad"
     if "compress_rows_bf16" in kernel_name and a[:1] == ["4"]:
         if a[1] == "true":

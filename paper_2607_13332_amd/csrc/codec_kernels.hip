@@ -933,7 +933,7 @@ bool compress_uses_mfma(int dtype, int64_t d, int64_t k) {
 }
 
 bool decompress_uses_mfma(int dtype, int64_t d, int64_t k) {
-  return dtype == kBF16 && d % (2 * kDecompressDC) == 0 && d <= INT32_MAX && k >= 1 && k <= 128;
+  return dtype == kBF16 && d % 128 == 0 && d <= INT32_MAX && k >= 1 && k <= 128;
 }
 
 // Row-contiguous kernel: 8 waves (128 tokens) per block with a rotated sweep
@@ -1313,7 +1313,7 @@ hipError_t launch_project_ranges(int dtype, int64_t N, int64_t d, int64_t k, con
 // fills at least 90 % of the blocks' last round, else the smallest that
 // reaches one block per unit (N = 12288, d = 5120, k = 51: 96 blocks in 5
 // ranges 57.9 us, in 4 ranges 64.3 us).
-int decompress_grid_split(int64_t blocks, int chunks) {
+static int decompress_grid_split(int64_t blocks, int chunks) {
   const int64_t cus = device_cu_count();
   int gy = 1;
   if (blocks < cus) {
@@ -1332,7 +1332,7 @@ int decompress_grid_split(int64_t blocks, int chunks) {
   return gy;
 }
 
-template <int KS2, bool HAS_E, int KM, bool GZ>
+template <int KS2, bool HAS_E, int KM>
 static hipError_t launch_decompress_km(int64_t N, int d, int k, int64_t V, const float* Zc,
                                        const int32_t* ids, const void* E, const void* U, void* Y,
                                        hipStream_t st, const uint16_t* Zb, int kz) {
@@ -1342,36 +1342,43 @@ static hipError_t launch_decompress_km(int64_t N, int d, int k, int64_t V, const
   const int gy = decompress_grid_split(blocks, chunks);
   const dim3 grid((unsigned)blocks, (unsigned)gy);
   if (!HAS_E && (chunks / gy) % 2 == 0)
-    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, GZ, false,
+    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, false, false,
                                              1, 2>),
                        grid, dim3(64 * TW), 0, st, Zc, ids, (const uint16_t*)E, (const uint16_t*)U,
                        (uint16_t*)Y, N, d, k, V, Zb, kz);
   else
-    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, GZ>), grid,
+    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true>), grid,
                        dim3(64 * TW), 0, st, Zc, ids, (const uint16_t*)E, (const uint16_t*)U,
                        (uint16_t*)Y, N, d, k, V, Zb, kz);
   return hipGetLastError();
 }
 
-template <int KS2, bool HAS_E, bool GZ>
-static hipError_t launch_decompress_ks(int64_t N, int d, int k, int64_t V, const float* Zc,
-                                       const int32_t* ids, const void* E, const void* U, void* Y,
-                                       hipStream_t st, const uint16_t* Zb, int kz) {
-  if (k == 32 * KS2) return launch_decompress_km<KS2, HAS_E, 0, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-  if (k % 8 == 0) return launch_decompress_km<KS2, HAS_E, 1, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-  return launch_decompress_km<KS2, HAS_E, 2, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+template <int KS2, bool HAS_E>
+static hipError_t launch_chunks_ks(int64_t N, int d, int k, int64_t V, const float* Zc,
+                                   const int32_t* ids, const void* E, const void* U, void* Y,
+                                   hipStream_t st, const uint16_t* Zb, int kz) {
+  if (k == 32 * KS2) return launch_decompress_km<KS2, HAS_E, 0>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+  if (k % 8 == 0) return launch_decompress_km<KS2, HAS_E, 1>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+  return launch_decompress_km<KS2, HAS_E, 2>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
 }
 
-template <bool HAS_E, bool GZ>
-static hipError_t launch_decompress_mfma(int64_t N, int d, int k, int64_t V, const float* Zc,
-                                         const int32_t* ids, const void* E, const void* U, void* Y,
-                                         hipStream_t st, const uint16_t* Zb, int kz) {
-  switch ((k + 31) / 32) {
-    case 1: return launch_decompress_ks<1, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-    case 2: return launch_decompress_ks<2, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-    case 3: return launch_decompress_ks<3, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-    default: return launch_decompress_ks<4, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-  }
+// Where the chunk-staged kernel runs: k <= 64 and more tokens than the
+// token-split form of the column kernel takes, up to 8192.  There a block of
+// the column kernel walks only 4 to 20 tiles for the U it fetches first:
+// Pluralis-8B's step at N = 4096, d = 5120 takes 76.6 us on this kernel and
+// 78.1 on that, and the reparameterized layer at N = 4096, din = 18432 155.6
+// against 160.1; at N = 12205, d = 5120 it is 186.7 against 174.4.
+static bool decompress_uses_chunks(int64_t N, int64_t d, int64_t k) {
+  const int64_t nd = (d + 511) / 512, slots = 2 * (int64_t)device_cu_count();
+  return k <= 64 && N <= 8192 && (N + 15) / 16 > 3 * (slots / nd);
+}
+
+template <bool HAS_E>
+static hipError_t launch_chunks(int64_t N, int d, int k, int64_t V, const float* Zc,
+                                const int32_t* ids, const void* E, const void* U, void* Y,
+                                hipStream_t st, const uint16_t* Zb, int kz) {
+  return k <= 32 ? launch_chunks_ks<1, HAS_E>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz)
+                 : launch_chunks_ks<2, HAS_E>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
 }
 
 template <typename T, bool HAS_E, bool GZ>
@@ -1395,9 +1402,10 @@ hipError_t launch_decompress(int dtype, int64_t N, int64_t d, int64_t k, int64_t
     return launch_decompress_f32(N, d, k, V, Zc, ids, (const float*)E, (const float*)U, (float*)Y,
                                  gather_z, st, Zb, kz);
   if (decompress_uses_mfma(dtype, d, k) && al16(zin) && al16(U) && al16(Y) && (!has_e || al16(E))) {
-    if (has_e) return launch_decompress_mfma<true, false>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
-    if (gather_z) return launch_decompress_mfma<false, true>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
-    return launch_decompress_mfma<false, false>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
+    if (!gather_z && decompress_uses_chunks(N, d, k))
+      return has_e ? launch_chunks<true>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz)
+                   : launch_chunks<false>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
+    return launch_decompress_bf16(N, d, k, V, Zc, ids, E, U, Y, gather_z, st, Zb, kz);
   }
   if (dtype == kF32) {
     if (has_e) return launch_decompress_generic<float, true, false>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz64);
