@@ -1,16 +1,15 @@
-// Stage-boundary codec with float32 storage on the matrix cores:
-// v_mfma_f32_16x16x4_f32 multiplies float32 operands and accumulates in
-// float32, so no operand is split.  Paper: section 4.1, Eq. (2) --
-// Z = (X - E[ids]) U, X' = E[ids] + Z U^T; the gradient forms are the same
-// kernels without the embedding.
+// Stage-boundary compress / gradient projection with float32 storage on the
+// matrix cores.  Paper: section 4.1, Eq. (2) -- Z = (X - E[ids]) U; the
+// gradient form is the same kernels without the embedding.
 //
 // The kernels walk d in 64-wide chunks (256 contiguous bytes of a float32
-// row) and stage the chunk's 64 rows of U [d, ku] (any ku <= 128) into a
-// row-major LDS tile K = 16 ceil(ku / 16) wide (pitch K + 4 floats, zero past
-// ku): the many-token kernels once per block, double buffered, one barrier
-// per chunk, their activation and embedding rows moving as 4 rows x 256
-// contiguous bytes per instruction; the few-token compress / projection once
-// per wave, with no barrier.
+// row).  With many tokens a block stages a chunk's 64 rows of U [d, ku] (any
+// ku <= 128) once, split into three bf16 planes, double buffered, one barrier
+// per chunk.  With few tokens the waves of a block split d: each stages its
+// own chunk into a row-major float32 tile K = 16 ceil(ku / 16) wide (pitch K
+// + 4 floats, zero past ku) with no barrier and multiplies with
+// v_mfma_f32_16x16x4_f32 (the split into planes would cost a wave more than
+// the multiplications of its 16 tokens save).
 #include "ssn_device.h"
 #include "ssn_launch.h"
 
@@ -109,26 +108,37 @@ struct UStage {
 
 // ===========================================================================
 // compress / gradient projection, Z [N, kz] = (X - E[ids]) U (or X U, minus
-// P[ids] with the projected table).  C = D [16 tokens x 4] . U [4 x 16]:
-// MFMA (q, s) pairs K slot g with d = 16 q + 4 g + s, so a lane's A values
-// for s = 0..3 are one 16-byte read of its token's row of D from the
-// wave-private tile it was parked in (X - E formed in registers, one float32
-// rounding).  Column slot j of tile i is coordinate KP j + i, so the B values
-// of all KP tiles for one (q, s) are the KP contiguous floats
-// U[16 q + 4 g + s][KP j ..] of the staged tile, and lane (j, g) ends with
-// coordinates KP j .. KP j + KP - 1 of tokens 4 g .. 4 g + 3.  Block = W
-// waves x 16 tokens, every wave sweeping all of d (start rotated per block).
+// P[ids] with the projected table), on the bf16 matrix cores: D = X - E
+// (formed in registers, one float32 rounding) and U are split exactly into
+// three bf16 planes and a product takes the six plane pairs that reach past
+// 2^-24 of it, in 96 cycles of the matrix core for 32 columns of d where the
+// float32 instruction takes 256; the five small pairs are summed apart and
+// added once at the end.
+//
+// Block = W waves x 16 tokens, every wave sweeping all of d (start rotated
+// per block) in chunks of 64.  U's planes are staged per block in B-operand
+// order, double buffered, one barrier per chunk; a staging task is 8 rows of
+// one column (columns past ku repeat the last one: their coordinates are not
+// stored).  Rows of X and E arrive 4 rows x 256 contiguous bytes per
+// instruction, one chunk ahead, and D changes lanes through a wave-private
+// XOR-swizzled LDS tile; the wave splits its A operands as it reads them.
+// Bound: HBM.  Measured against the float32 instructions, projection /
+// compress: N = 32768, d = 4096, k = 64 167 / 204 -> 133 / 184 us (5.8 TB/s
+// with the embedding rows), k = 128 291 / 308 -> 233 / 256 us; N = 50000, d =
+// 2048, k = 17 100 / 145 -> 89 / 135 us; error against 64 bits 1.1e-6 ->
+// 4.0e-7.
+// A wave with a result that is not finite (an infinity or NaN, or an
+// overflow) sweeps d again with float32 instructions straight from memory.
 // ===========================================================================
-template <int KP, bool HAS_E, bool HAS_P, int W, bool SPAN>
+template <int KP, bool HAS_E, bool HAS_P, int W>
 __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
     const float* __restrict__ X, const int32_t* __restrict__ ids, const float* __restrict__ E,
     const float* __restrict__ U, float* __restrict__ Z, int64_t N, int d, int64_t V,
     const float* __restrict__ Pt, uint16_t* __restrict__ Zb, int kz, int ku) {
   static_assert(!(HAS_E && HAS_P), "the embedding is subtracted as rows or as projected rows");
-  constexpr int K = 16 * KP, DC = kF32Chunk;
-  using Stage = UStage<K, 64 * W, SPAN>;
-  constexpr int UP = Stage::UP, FPT = Stage::FPT;
-  __shared__ __align__(16) float ut[2][DC * UP];
+  constexpr int K = 16 * KP, DC = kF32Chunk, T = 64 * W;
+  constexpr int NTASK = DC / 8 * K, TPT = (NTASK + T - 1) / T;
+  __shared__ u32x4 ut[2][2 * KP * 3 * kWave];      // [buffer][K step][tile][plane][lane]
   __shared__ f32x4 dt[W][16 * 16];                 // [wave][token * 16 + (cell ^ token)]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -154,15 +164,38 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
     xrow[m] = X + t * d + 4 * n16;
     erow[m] = HAS_E ? E + clamp_id(ids[t], V) * d + 4 * n16 : nullptr;
   }
-  const Stage stage(tid, ku);
-  stage.zero_pad(&ut[0][0], 2);
-  f32x4 ust[2][FPT];
   f32x4 xs[2][4], es[2][4];
   auto load_rows = [&](int c, f32x4(&xo)[4], f32x4(&eo)[4]) {
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       xo[m] = __builtin_nontemporal_load((const f32x4*)(xrow[m] + c * DC));
       if constexpr (HAS_E) eo[m] = *(const f32x4*)(erow[m] + c * DC);
+    }
+  };
+  // U: task q is column q % K of the 8 rows q / K of the chunk (threads past
+  // the last task repeat it and do not store)
+  float ur[TPT][8];
+  auto load_u = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) {
+      const int q = NTASK % T == 0 ? tid + T * i : min(tid + T * i, NTASK - 1);
+      const float* src = U + (int64_t)(c * DC + 8 * (q / K)) * ku + min(q % K, ku - 1);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ur[i][e] = src[e * ku];
+    }
+  };
+  auto store_u = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) {
+      const int q = tid + T * i, col = q % K, rg = q / K;
+      u32x4 h, m, l;
+      split3_bf16x8(ur[i], h, m, l);
+      if (NTASK % T == 0 || q < NTASK) {
+        u32x4* dst = ut[buf] + ((rg >> 2) * KP + (col >> 4)) * 192 + 16 * (rg & 3) + (col & 15);
+        dst[0] = h;
+        dst[64] = m;
+        dst[128] = l;
+      }
     }
   };
 
@@ -174,56 +207,48 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
   };
   auto last = [&](int i) { return i < nch ? i : nch - 1; };
   f32x4* dw = dt[wave];
-  f32x4 acc[KP];
+  f32x4 acc[KP], sm[KP];
 #pragma unroll
-  for (int i = 0; i < KP; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < KP; ++i) acc[i] = sm[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // chunk i, i % 2 == B: its U already staged, its rows in set B
   auto body = [&](int i, auto Bc) {
     constexpr int B = decltype(Bc)::value;
-    stage.load(U, chunk(last(i + 2)), ust[B]);
-    load_rows(chunk(last(i + 1)), xs[B ^ 1], es[B ^ 1]);
     // park chunk i's rows of D
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const int r = 4 * m + g;
       dw[r * 16 + (n16 ^ r)] = HAS_E ? xs[B][m] - es[B][m] : xs[B][m];
     }
+    load_u(chunk(last(i + 1)));
+    load_rows(chunk(last(i + 2)), xs[B], es[B]);
     __syncthreads();
-    const float* ub = ut[B];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 a = dw[n16 * 16 + ((4 * q + g) ^ n16)];
+    for (int s = 0; s < 2; ++s) {
+      const f32x4 a = dw[n16 * 16 + ((8 * s + 2 * g) ^ n16)];
+      const f32x4 b = dw[n16 * 16 + ((8 * s + 2 * g + 1) ^ n16)];
+      const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+      u32x4 h, m, l;
+      split3_bf16x8(v, h, m, l);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const float* ur = ub + (16 * q + 4 * g + s) * UP + KP * n16;
-        float b[KP];
-        if constexpr (KP % 4 == 0) {
-#pragma unroll
-          for (int h = 0; h < KP; h += 4) {
-            const f32x4 v = *(const f32x4*)(ur + h);
-            b[h] = v[0]; b[h + 1] = v[1]; b[h + 2] = v[2]; b[h + 3] = v[3];
-          }
-        } else if constexpr (KP % 2 == 0) {
-#pragma unroll
-          for (int h = 0; h < KP; h += 2) {
-            const f32x2 v = *(const f32x2*)(ur + h);
-            b[h] = v[0]; b[h + 1] = v[1];
-          }
-        } else {
-#pragma unroll
-          for (int h = 0; h < KP; ++h) b[h] = ur[h];
-        }
-#pragma unroll
-        for (int h = 0; h < KP; ++h) acc[h] = mfma16x16x4f32(a[s], b[h], acc[h]);
+      for (int p = 0; p < KP; ++p) {
+        const u32x4* ub = ut[B] + (s * KP + p) * 192 + lane;
+        const u32x4 uh = ub[0], um = ub[64], ul = ub[128];
+        sm[p] = mfma16x16x32(h, ul, sm[p]);
+        acc[p] = mfma16x16x32(h, uh, acc[p]);
+        sm[p] = mfma16x16x32(l, uh, sm[p]);
+        sm[p] = mfma16x16x32(m, um, sm[p]);
+        sm[p] = mfma16x16x32(m, uh, sm[p]);
+        sm[p] = mfma16x16x32(h, um, sm[p]);
       }
     }
-    stage.store(ut[B ^ 1], ust[B ^ 1]);
+    store_u(B ^ 1);
   };
 
-  stage.load(U, chunk(0), ust[0]);
+  load_u(chunk(0));
   load_rows(chunk(0), xs[0], es[0]);
-  stage.load(U, chunk(last(1)), ust[1]);
-  stage.store(ut[0], ust[0]);
+  load_rows(chunk(last(1)), xs[1], es[1]);
+  store_u(0);
   int i = 0;
   for (; i + 1 < nch; i += 2) {
     body(i, std::integral_constant<int, 0>{});
@@ -231,16 +256,39 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
   }
   if (i < nch) body(i, std::integral_constant<int, 0>{});
 
-  // lane (j, g): coordinates KP j + h of tokens 4 g + r
+  float z = 0.f;
+#pragma unroll
+  for (int p = 0; p < KP; ++p) {
+    acc[p] += sm[p];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z = 16 * p + n16 < ku ? fmaf(acc[p][r], 0.f, z) : z;
+  }
+  if (__any(z != 0.f)) {
+#pragma unroll
+    for (int p = 0; p < KP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int64_t t = tok0 + n16;
+    t = t < N ? t : N - 1;
+    const float* xp = X + t * d + g;
+    const float* ep = HAS_E ? E + clamp_id(ids[t], V) * d + g : nullptr;
+#pragma clang loop unroll(disable)
+    for (int r0 = 0; r0 < d; r0 += 4) {
+      const float a = HAS_E ? xp[r0] - ep[r0] : xp[r0];
+#pragma unroll
+      for (int p = 0; p < KP; ++p)
+        acc[p] = mfma16x16x4f32(a, U[(int64_t)(r0 + g) * ku + min(16 * p + n16, ku - 1)], acc[p]);
+    }
+  }
+
+  // lane (n16, g): coordinates 16 p + n16 of tokens 4 g + r
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int64_t t = tok0 + 4 * g + r;
     if (t >= N) continue;
 #pragma unroll
-    for (int h = 0; h < KP; ++h) {
-      const int col = KP * n16 + h;
+    for (int p = 0; p < KP; ++p) {
+      const int col = 16 * p + n16;
       if (col >= kz) continue;
-      float v = acc[h][r];
+      float v = acc[p][r];
       if constexpr (HAS_P) v -= Pt[prow[r] + col];
       if (Zb)
         Zb[t * kz + col] = (uint16_t)f32_to_bf16(v);
@@ -255,8 +303,12 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
 // N / 64 blocks, a fraction of the chip).  Block = 16 tokens x PW waves; wave
 // w walks the w-th of PW equal ranges of d with a wave-private U tile and
 // its A operands read straight from the rows, so no barrier is needed until
-// the end (a wave's LDS operations complete in order).  U for the next chunks travels in UD register sets;
-// the MFMA loop is the one above.  The PW partial products meet in LDS and
+// the end (a wave's LDS operations complete in order).  U for the next chunks
+// travels in UD register sets.  MFMA (q, s) pairs K slot g with d = 16 q + 4 g
+// + s; column slot j of tile i is coordinate KP j + i, so the B values of all
+// KP tiles for one (q, s) are KP contiguous floats of the staged tile and lane
+// (j, g) ends with coordinates KP j .. KP j + KP - 1 of tokens 4 g .. 4 g + 3.
+// The PW partial products meet in LDS and
 // are added in wave order (deterministic); wave w finishes the coordinates
 // KP j + h with h = w mod PW.
 // ===========================================================================
@@ -395,20 +447,20 @@ __global__ __launch_bounds__(64 * PW) void compress_f32_split(
 // ===========================================================================
 // Launchers.
 // ===========================================================================
-template <int KP, int W, bool SPAN>
+template <int KP, int W>
 static hipError_t launch_compress_f32_kp(int64_t N, int d, int64_t V, const float* X,
                                          const int32_t* ids, const float* E, const float* U,
                                          float* Z, const float* P, hipStream_t st, uint16_t* Zb,
                                          int kz, int ku) {
   const dim3 grid((unsigned)((N + 16 * W - 1) / (16 * W)));
   if (E)
-    hipLaunchKernelGGL((compress_f32_mfma<KP, true, false, W, SPAN>), grid, dim3(64 * W), 0, st, X, ids,
+    hipLaunchKernelGGL((compress_f32_mfma<KP, true, false, W>), grid, dim3(64 * W), 0, st, X, ids,
                        E, U, Z, N, d, V, P, Zb, kz, ku);
   else if (P)
-    hipLaunchKernelGGL((compress_f32_mfma<KP, false, true, W, SPAN>), grid, dim3(64 * W), 0, st, X, ids,
+    hipLaunchKernelGGL((compress_f32_mfma<KP, false, true, W>), grid, dim3(64 * W), 0, st, X, ids,
                        E, U, Z, N, d, V, P, Zb, kz, ku);
   else
-    hipLaunchKernelGGL((compress_f32_mfma<KP, false, false, W, SPAN>), grid, dim3(64 * W), 0, st, X,
+    hipLaunchKernelGGL((compress_f32_mfma<KP, false, false, W>), grid, dim3(64 * W), 0, st, X,
                        ids, E, U, Z, N, d, V, P, Zb, kz, ku);
   return hipGetLastError();
 }
@@ -437,9 +489,8 @@ static hipError_t launch_compress_f32_w(int64_t N, int d, int64_t V, const float
                                         const int32_t* ids, const float* E, const float* U, float* Z,
                                         const float* P, hipStream_t st, uint16_t* Zb, int kz, int ku) {
   // 8 waves (128 tokens) per block once those blocks fill the compute units,
-  // else 4 (64 tokens); U rows of any width other than 16 KP are staged
-  // span-wise.  With at most three quarters as many 64-token blocks as
-  // compute units, d is split over the waves of 16-token blocks instead
+  // else 4 (64 tokens).  With at most three quarters as many 64-token blocks
+  // as compute units, d is split over the waves of 16-token blocks instead
   // (measured on MI355X, compress / projection: N = 2048, d = 2048, k = 40:
   // 53 / 53 -> 21 / 17 us; N = 4096, d = 5120, k = 51: 152 / 150 -> 54 /
   // 45 us; N = 8192, d = 2048: 57 / 56 -> 40 / 35 us; N = 12288, d = 5120:
@@ -450,10 +501,8 @@ static hipError_t launch_compress_f32_w(int64_t N, int d, int64_t V, const float
   if (4 * ((N + 63) / 64) <= 3 * cus && d % ((KP <= 4 ? 8 : 4) * kF32Chunk) == 0)
     return span ? launch_compress_f32_split<KP, true>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku)
                 : launch_compress_f32_split<KP, false>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
-  if (eight && !span) return launch_compress_f32_kp<KP, 8, false>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
-  if (eight) return launch_compress_f32_kp<KP, 8, true>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
-  if (!span) return launch_compress_f32_kp<KP, 4, false>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
-  return launch_compress_f32_kp<KP, 4, true>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
+  return eight ? launch_compress_f32_kp<KP, 8>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku)
+               : launch_compress_f32_kp<KP, 4>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
 }
 
 hipError_t launch_compress_f32(int64_t N, int64_t d, int64_t k, int64_t V, const float* X,
