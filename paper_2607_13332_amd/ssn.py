@@ -156,7 +156,7 @@ def _stream(stream) -> int:
         if _raw_current_stream is not None:
             # the raw handle directly (torch.cuda.current_stream() builds a
             # Stream object per call, a few microseconds)
-            return int(_raw_current_stream(torch.cuda.current_device()))
+            return _raw_current_stream(_get_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
@@ -173,6 +173,26 @@ def _dev(t: torch.Tensor, name: str, dtype=None, ndim=None):
     if ndim is not None and t.dim() != ndim:
         raise ValueError(f"{name} must have {ndim} dims, got shape {tuple(t.shape)}")
     return t.data_ptr()
+
+
+_CODES = {torch.float32: SSN_F32, torch.bfloat16: SSN_BF16}
+_get_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+
+
+def _gpu(t: torch.Tensor, name: str, first: torch.Tensor, dev: int, dtype, ndim: int) -> int:
+    """data_ptr of a tensor that has to be contiguous, of `dtype` and `ndim`,
+    on the GPU `dev` of the call's `first` tensor: _dev and _same_device in one
+    look (the codec's calls take microseconds, and so does each property read
+    of a tensor); anything wrong is named by those two."""
+    if t.get_device() != dev or t.dtype != dtype or t.dim() != ndim or not t.is_contiguous() or dev < 0:
+        _same_device(first, t)
+        return _dev(t, name, dtype, ndim)
+    return t.data_ptr()
+
+
+def _code(dtype) -> int:
+    c = _CODES.get(dtype)
+    return _dt_code(dtype) if c is None else c
 
 
 def _same_device(*ts):
@@ -194,12 +214,11 @@ def compress(X: torch.Tensor, ids: torch.Tensor, E: torch.Tensor, U: torch.Tenso
                          f"E{tuple(E.shape)} U{tuple(U.shape)}")
     if out is None:
         out = torch.empty((N, k), dtype=z_dtype, device=X.device)
-    _same_device(X, ids, E, U, out)
-    t = X.dtype
+    t, g = X.dtype, X.get_device()
     _check("ssn_compress_ex", lib().ssn_compress_ex(
-        _dt_code(t), _dt_code(z_dtype), N, d, k, V, _dev(X, "X", t, 2),
-        _dev(ids, "ids", torch.int32, 1), _dev(E, "E", t, 2), _dev(U, "U", t, 2), ldu,
-        _dev(out, "out", z_dtype, 2), _stream(stream)))
+        _code(t), _code(z_dtype), N, d, k, V, _gpu(X, "X", X, g, t, 2),
+        _gpu(ids, "ids", X, g, torch.int32, 1), _gpu(E, "E", X, g, t, 2), _gpu(U, "U", X, g, t, 2), ldu,
+        _gpu(out, "out", X, g, z_dtype, 2), _stream(stream)))
     return out
 
 
@@ -222,12 +241,12 @@ def decompress(Z: torch.Tensor, ids: Optional[torch.Tensor], E: Optional[torch.T
             raise ValueError(f"shape mismatch E{tuple(E.shape)} ids{tuple(ids.shape)}")
     if out is None:
         out = torch.empty((N, d), dtype=t, device=Z.device)
-    _same_device(Z, ids, E, U, out)
+    zt, g = Z.dtype, Z.get_device()
     _check("ssn_decompress_ex", lib().ssn_decompress_ex(
-        _dt_code(t), _dt_code(Z.dtype), N, d, k, V, _dev(Z, "Z", Z.dtype, 2),
-        None if ids is None else _dev(ids, "ids", torch.int32, 1),
-        None if E is None else _dev(E, "E", t, 2), _dev(U, "U", t, 2), ldu,
-        _dev(out, "out", t, 2), _stream(stream)))
+        _code(t), _code(zt), N, d, k, V, _gpu(Z, "Z", Z, g, zt, 2),
+        None if ids is None else _gpu(ids, "ids", Z, g, torch.int32, 1),
+        None if E is None else _gpu(E, "E", Z, g, t, 2), _gpu(U, "U", Z, g, t, 2), ldu,
+        _gpu(out, "out", Z, g, t, 2), _stream(stream)))
     return out
 
 
@@ -251,17 +270,15 @@ def project_grad(G: torch.Tensor, U: torch.Tensor, out: Optional[torch.Tensor] =
         raise ValueError(f"shape mismatch G{tuple(G.shape)} U{tuple(U.shape)}")
     if out is None:
         out = torch.empty((N, k), dtype=z_dtype, device=G.device)
-    _same_device(G, U, out)
-    t = G.dtype
+    t, g = G.dtype, G.get_device()
     if workspace is None:
         _check("ssn_project_grad_ex", lib().ssn_project_grad_ex(
-            _dt_code(t), _dt_code(z_dtype), N, d, k, _dev(G, "G", t, 2), _dev(U, "U", t, 2), ldu,
-            _dev(out, "out", z_dtype, 2), _stream(stream)))
+            _code(t), _code(z_dtype), N, d, k, _gpu(G, "G", G, g, t, 2), _gpu(U, "U", G, g, t, 2), ldu,
+            _gpu(out, "out", G, g, z_dtype, 2), _stream(stream)))
         return out
-    _same_device(G, workspace)
     _check("ssn_project_grad_ws", lib().ssn_project_grad_ws(
-        _dt_code(t), _dt_code(z_dtype), N, d, k, _dev(G, "G", t, 2), _dev(U, "U", t, 2), ldu,
-        _dev(out, "out", z_dtype, 2), _dev(workspace, "workspace", torch.uint8, 1),
+        _code(t), _code(z_dtype), N, d, k, _gpu(G, "G", G, g, t, 2), _gpu(U, "U", G, g, t, 2), ldu,
+        _gpu(out, "out", G, g, z_dtype, 2), _gpu(workspace, "workspace", G, g, torch.uint8, 1),
         workspace.numel(), _stream(stream)))
     return out
 
@@ -344,12 +361,11 @@ def compress_projected(X: torch.Tensor, ids: torch.Tensor, P: torch.Tensor, U: t
                          f"P{tuple(P.shape)} U{tuple(U.shape)}")
     if out is None:
         out = torch.empty((N, k), dtype=z_dtype, device=X.device)
-    _same_device(X, ids, P, U, out)
-    t = X.dtype
+    t, g = X.dtype, X.get_device()
     _check("ssn_compress_projected_ex", lib().ssn_compress_projected_ex(
-        _dt_code(t), _dt_code(z_dtype), N, d, k, V, _dev(X, "X", t, 2),
-        _dev(ids, "ids", torch.int32, 1), _dev(P, "P", torch.float32, 2), _dev(U, "U", t, 2),
-        ldu, _dev(out, "out", z_dtype, 2), _stream(stream)))
+        _code(t), _code(z_dtype), N, d, k, V, _gpu(X, "X", X, g, t, 2),
+        _gpu(ids, "ids", X, g, torch.int32, 1), _gpu(P, "P", X, g, torch.float32, 2),
+        _gpu(U, "U", X, g, t, 2), ldu, _gpu(out, "out", X, g, z_dtype, 2), _stream(stream)))
     return out
 
 
