@@ -489,16 +489,15 @@ static hipError_t launch_compress_f32_w(int64_t N, int d, int64_t V, const float
                                         const int32_t* ids, const float* E, const float* U, float* Z,
                                         const float* P, hipStream_t st, uint16_t* Zb, int kz, int ku) {
   // 8 waves (128 tokens) per block once those blocks fill the compute units,
-  // else 4 (64 tokens).  With at most three quarters as many 64-token blocks
-  // as compute units, d is split over the waves of 16-token blocks instead
-  // (measured on MI355X, compress / projection: N = 2048, d = 2048, k = 40:
-  // 53 / 53 -> 21 / 17 us; N = 4096, d = 5120, k = 51: 152 / 150 -> 54 /
-  // 45 us; N = 8192, d = 2048: 57 / 56 -> 40 / 35 us; N = 12288, d = 5120:
-  // 167 / 182 -> 164 / 146 us; but N = 16384, d = 4096, k = 64: 130 / 108
-  // us on the 64-token blocks against 166 / 143 us split).
+  // else 4 (64 tokens).  With at most five eighths as many 64-token blocks as
+  // compute units (10240 tokens), d is split over the waves of 16-token blocks
+  // instead (measured on MI355X, projection / compress, split against 64-token
+  // blocks: N = 8200, d = 4096, k = 64 85 / 98 and 97 / 99 us; N = 9000, d =
+  // 2048, k = 40 43 / 53 and 47 / 53; N = 11000, d = 5120, k = 51 131 / 153
+  // and 122 / 124; N = 12000 122 / 148 and 122 / 124).
   const int64_t cus = device_cu_count();
   const bool eight = (N + 127) / 128 >= cus, span = ku != 16 * KP;
-  if (4 * ((N + 63) / 64) <= 3 * cus && d % ((KP <= 4 ? 8 : 4) * kF32Chunk) == 0)
+  if (8 * ((N + 63) / 64) <= 5 * cus && d % ((KP <= 4 ? 8 : 4) * kF32Chunk) == 0)
     return span ? launch_compress_f32_split<KP, true>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku)
                 : launch_compress_f32_split<KP, false>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
   return eight ? launch_compress_f32_kp<KP, 8>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku)
