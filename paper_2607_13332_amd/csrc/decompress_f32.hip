@@ -74,9 +74,10 @@ __global__ __launch_bounds__(64 * kExp32Waves, 2) void decompress_cols_f32(
   const int xcd = blockIdx.x & 7, xj = blockIdx.x >> 3;
   const int w = xcd * q8 + (xcd < r8 ? xcd : r8) + xj;
   const int range = w / nd;
-  const int colw = ((w - range * nd) * NW + wave) * CW;
-  const bool live = colw < d;                    // others only help with the staging
-  const int col0 = live ? colw : 0;
+  // (unsigned: the last block's columns may pass 2^31)
+  const uint32_t colw = (uint32_t)((w - range * nd) * NW + wave) * CW;
+  const bool live = colw < (uint32_t)d;          // others only help with the staging
+  const int col0 = live ? (int)colw : 0;
   // per or per + 1 tiles (divided on the host: a 64-bit division here took
   // about as long as the smallest launches' loads)
   const int n = per + (range < more ? 1 : 0);
@@ -291,7 +292,7 @@ static hipError_t launch_cols(int64_t N, int d, int k, int64_t V, const float* Z
                               const int32_t* ids, const float* E, const float* U, float* Y, int kz,
                               hipStream_t st) {
   constexpr int BC = kExp32Waves * 16 * exp32_tiles(KS);
-  const int64_t tiles = (N + 15) / 16, nd = (d + BC - 1) / BC;
+  const int64_t tiles = (N + 15) / 16, nd = ((int64_t)d + BC - 1) / BC;
   int64_t ranges = 2 * (int64_t)device_cu_count() / nd;
   ranges = ranges < 1 ? 1 : (ranges < tiles ? ranges : tiles);
   hipLaunchKernelGGL((decompress_cols_f32<KS, HAS_E, GZ, ZB>), dim3((unsigned)(nd * ranges)),

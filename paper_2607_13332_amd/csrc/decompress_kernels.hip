@@ -76,9 +76,10 @@ __global__ __launch_bounds__(64 * kExpandWaves, 2) void decompress_cols_bf16(
   const int w = xcd * q8 + (xcd < r8 ? xcd : r8) + xj;
   const int range = w / nd;
   // waves past the last column only help with the staging
-  const int colw = ((w - range * nd) * (TS ? 1 : NW) + (TS ? 0 : wave)) * kExpandCols;
-  const bool live = TS || colw < d;
-  const int col0 = live ? colw : 0;
+  // (unsigned: the last block's columns may pass 2^31)
+  const uint32_t colw = (uint32_t)((w - range * nd) * (TS ? 1 : NW) + (TS ? 0 : wave)) * kExpandCols;
+  const bool live = TS || colw < (uint32_t)d;
+  const int col0 = live ? (int)colw : 0;
   // per or per + 1 tiles (divided on the host: a 64-bit division here took
   // about as long as the smallest launches' loads)
   const int n = per + (range < more ? 1 : 0);
@@ -342,7 +343,7 @@ static hipError_t launch_cols(int64_t N, int d, int k, int64_t V, const float* Z
     const int64_t r = slots / nd < 1 ? 1 : slots / nd;
     return r < most ? r : most;
   };
-  int64_t nd = (d + kExpandBlockCols - 1) / kExpandBlockCols, ranges = ranges_of(nd, tiles);
+  int64_t nd = ((int64_t)d + kExpandBlockCols - 1) / kExpandBlockCols, ranges = ranges_of(nd, tiles);
   if constexpr (KS <= 2) {
     if (tiles <= 3 * ranges) {
       nd = d / kExpandCols;
