@@ -26,9 +26,11 @@ struct TileVec<2> { typedef f32x2 T; };
 // What bounds it: the bytes of Y (and of the gathered rows of E); the float32
 // matrix instructions would not keep up with them (16x16x4: 32 cycles for
 // what six bf16 16x16x32 do in 12).  Every float32 operand is split exactly
-// into three bf16 planes and a product takes the six plane pairs that reach
-// past 2^-24 of it; the five small pairs are summed on their own and added
-// once at the end.  bf16 coordinates (ZB) are one plane, three pairs.
+// (scaled by 2^16) into three bf16 planes and a product takes the six plane
+// pairs that leave out at most 2^-24 of it, the five small pairs of all K
+// steps first.  The large ones go on from their sum, or (one K step, where
+// one rounding more counts) are summed apart and added once.  bf16
+// coordinates (ZB) are one plane, three pairs.
 //
 // A wave owns 16 NTL columns of Y whose rows of U stay in registers, split
 // once, as MFMA B fragments; the block walks its range of tokens in tiles of
@@ -122,7 +124,7 @@ __global__ __launch_bounds__(64 * kExp32Waves, 2) void decompress_cols_f32(
 #pragma unroll
         for (int m = 0; m < 8; ++m) v[m] = __uint_as_float(zr[m >> 2][m & 3]);
         u32x4 h, m, l;
-        split3_bf16x8(v, h, m, l);
+        split3_bf16x8<true>(v, h, m, l);
         dst[0][pdst] = h;
         dst[NP > 1 ? 1 : 0][pdst] = m;
         dst[NP > 2 ? 2 : 0][pdst] = l;
@@ -195,42 +197,54 @@ __global__ __launch_bounds__(64 * kExp32Waves, 2) void decompress_cols_f32(
       const f32x4* src = &ut[wave][((NTL * n16 + tt) * UPITCH + 8 * g) / 4];
       const f32x4 a = src[0], b = src[1];
       const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-      split3_bf16x8(v, ub[s][tt][0], ub[s][tt][1], ub[s][tt][2]);
+      split3_bf16x8<true>(v, ub[s][tt][0], ub[s][tt][1], ub[s][tt][2]);
     }
   }
   store_z(0);
 
   auto step = [&](int i, const u32x4 (&zt)[KS][NP][kWave]) __attribute__((always_inline)) {
-    f32x4 acc[NTL], sm[NTL];
+    f32x4 acc[NTL];
 #pragma unroll
-    for (int tt = 0; tt < NTL; ++tt) acc[tt] = sm[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int tt = 0; tt < NTL; ++tt) acc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int cell = 16 * g + (n16 ^ (4 * s + g));
       const u32x4 zh = zt[s][0][cell];
 #pragma unroll
-      for (int tt = 0; tt < NTL; ++tt) sm[tt] = mfma16x16x32(zh, ub[s][tt][2], sm[tt]);
+      for (int tt = 0; tt < NTL; ++tt) acc[tt] = mfma16x16x32(zh, ub[s][tt][2], acc[tt]);
       if constexpr (!ZB) {
         const u32x4 zm = zt[s][NP > 1 ? 1 : 0][cell], zo = zt[s][NP > 2 ? 2 : 0][cell];
 #pragma unroll
-        for (int tt = 0; tt < NTL; ++tt) sm[tt] = mfma16x16x32(zo, ub[s][tt][0], sm[tt]);
+        for (int tt = 0; tt < NTL; ++tt) acc[tt] = mfma16x16x32(zo, ub[s][tt][0], acc[tt]);
 #pragma unroll
-        for (int tt = 0; tt < NTL; ++tt) sm[tt] = mfma16x16x32(zm, ub[s][tt][1], sm[tt]);
+        for (int tt = 0; tt < NTL; ++tt) acc[tt] = mfma16x16x32(zm, ub[s][tt][1], acc[tt]);
 #pragma unroll
-        for (int tt = 0; tt < NTL; ++tt) sm[tt] = mfma16x16x32(zm, ub[s][tt][0], sm[tt]);
+        for (int tt = 0; tt < NTL; ++tt) acc[tt] = mfma16x16x32(zm, ub[s][tt][0], acc[tt]);
       }
 #pragma unroll
-      for (int tt = 0; tt < NTL; ++tt) sm[tt] = mfma16x16x32(zh, ub[s][tt][1], sm[tt]);
-#pragma unroll
-      for (int tt = 0; tt < NTL; ++tt) acc[tt] = mfma16x16x32(zh, ub[s][tt][0], acc[tt]);
+      for (int tt = 0; tt < NTL; ++tt) acc[tt] = mfma16x16x32(zh, ub[s][tt][1], acc[tt]);
     }
+    if constexpr (KS == 1) {
+      const u32x4 zh = zt[0][0][16 * g + (n16 ^ g)];
+#pragma unroll
+      for (int tt = 0; tt < NTL; ++tt) acc[tt] += mfma16x16x32(zh, ub[0][tt][0], f32x4{0.f, 0.f, 0.f, 0.f});
+    } else {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const u32x4 zh = zt[s][0][16 * g + (n16 ^ (4 * s + g))];
+#pragma unroll
+        for (int tt = 0; tt < NTL; ++tt) acc[tt] = mfma16x16x32(zh, ub[s][tt][0], acc[tt]);
+      }
+    }
+    // bf16 coordinates entered as they are, U scaled
+    constexpr float unscale = 1.f / (ZB ? kPlanesScale : kPlanesScale * kPlanesScale);
     const int64_t t = tok0 + 16 * (int64_t)i + 4 * g;
     float z = 0.f;
 #pragma unroll
     for (int tt = 0; tt < NTL; ++tt) {
-      acc[tt] += sm[tt];
 #pragma unroll
       for (int j = 0; j < 4; ++j) z = fmaf(acc[tt][j], 0.f, z);
+      acc[tt] *= unscale;
     }
     if (__any(z != 0.f)) {
       // not finite: the tile again, in float32 from memory

@@ -110,8 +110,8 @@ struct UStage {
 // compress / gradient projection, Z [N, kz] = (X - E[ids]) U (or X U, minus
 // P[ids] with the projected table), on the bf16 matrix cores: D = X - E
 // (formed in registers, one float32 rounding) and U are split exactly into
-// three bf16 planes and a product takes the six plane pairs that reach past
-// 2^-24 of it, in 96 cycles of the matrix core for 32 columns of d where the
+// three bf16 planes and a product takes the six plane pairs that leave out at
+// most 2^-24 of it, in 96 cycles of the matrix core for 32 columns of d where the
 // float32 instruction takes 256; the five small pairs are summed apart and
 // added once at the end.
 //
@@ -127,8 +127,9 @@ struct UStage {
 // with the embedding rows), k = 128 291 / 308 -> 233 / 256 us; N = 50000, d =
 // 2048, k = 17 100 / 145 -> 89 / 135 us; error against 64 bits 1.1e-6 ->
 // 4.0e-7.
-// A wave with a result that is not finite (an infinity or NaN, or an
-// overflow) sweeps d again with float32 instructions straight from memory.
+// A wave with a result that the planes cannot vouch for (planes_unsure: an
+// infinity or NaN, an overflow, a result below 2^-80) sweeps d again with
+// float32 instructions straight from memory.
 // ===========================================================================
 template <int KP, bool HAS_E, bool HAS_P, int W>
 __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
@@ -256,14 +257,14 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
   }
   if (i < nch) body(i, std::integral_constant<int, 0>{});
 
-  float z = 0.f;
+  bool unsure = false;
 #pragma unroll
   for (int p = 0; p < KP; ++p) {
     acc[p] += sm[p];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) z = 16 * p + n16 < ku ? fmaf(acc[p][r], 0.f, z) : z;
+    for (int r = 0; r < 4; ++r) unsure |= 16 * p + n16 < ku && planes_unsure(acc[p][r]);
   }
-  if (__any(z != 0.f)) {
+  if (__any(unsure)) {
 #pragma unroll
     for (int p = 0; p < KP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
     int64_t t = tok0 + n16;

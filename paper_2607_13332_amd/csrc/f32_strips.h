@@ -18,8 +18,8 @@ namespace ssn {
 // step after each optimizer update, sections 4.1 and 6.1).
 //
 // Products: every float32 operand is split exactly into three bf16 planes
-// (split3_bf16x8) and a product takes the six plane pairs that reach past
-// 2^-24 of it, on the bf16 matrix cores: 6 instructions of 16x16x32 (96
+// (split3_bf16x8) and a product takes the six plane pairs that leave
+// out at most 2^-24 of it, on the bf16 matrix cores: 6 instructions of 16x16x32 (96
 // cycles) do the work of 8 of 16x16x4 in float32 (256 cycles).  The five
 // small pairs of a K step are summed on their own and added to the running
 // sum once, so a running sum is rounded twice per 32 products (the float32
@@ -43,9 +43,10 @@ namespace ssn {
 // registers that pass 1 left it in (split once), U's planes are staged in
 // that order, and a lane ends with rows 4 g + r of its NT columns: stored as
 // they are, 4 rows x 64 NT contiguous bytes per instruction (non-temporal).
-// A wave whose T is not finite (an infinity or NaN in W or U) redoes both
-// passes with float32 MFMAs straight from memory, which propagate them as
-// float32 arithmetic does.
+// A wave whose T the planes cannot vouch for (planes_unsure: an infinity or
+// NaN in W or U, an element below 2^-80) redoes both passes with float32 MFMAs
+// straight from memory, which propagate infinities and NaN as float32
+// arithmetic does.
 //
 // Bound: HBM, W read once and written once.  Measured on MI355X against the
 // kernel that multiplied float32 operands and passed W through LDS: 4 x
@@ -346,17 +347,17 @@ __global__ __launch_bounds__(64 * kS32Waves) void project_weights_f32_mfma(
       __syncthreads();                            // totals read before pass 2 stages U
     }
 
-    // an infinity or NaN anywhere in T: the strip's T again, in float32
+    // an element of T that the planes cannot vouch for (rows past k repeat
+    // row k - 1): the strip's T again, in float32
     bool bad = false;
     if constexpr (ON) {
-      float z = 0.f;
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) z = fmaf(acc[kt][i][r], 0.f, z);
-      bad = __any(z != 0.f);
+          for (int r = 0; r < 4; ++r) bad |= planes_unsure(acc[kt][i][r]);
+      bad = __any(bad);
       if (bad) {
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)

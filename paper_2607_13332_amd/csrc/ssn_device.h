@@ -68,25 +68,46 @@ __device__ __forceinline__ void split_bf16x8(const float* v, u32x4& hi, u32x4& l
   lo = u32x4{l[0], l[1], l[2], l[3]};
 }
 
-// Split 8 floats into three bf16 planes x = h + m + l, exactly: each plane is
-// the top 16 bits of what the planes before it leave (truncated, so that no
-// plane overflows), and 3 x 8 significant bits hold all 24 of a float32.  An
-// infinite x gives NaN in the lower planes (inf - inf): the kernels that use
-// the split recompute a non-finite result with float32 MFMAs.
+// Split 8 floats into three bf16 planes x = h + m + l: each plane is what the
+// planes before it leave, the first two rounded to nearest, and 3 x 8
+// significant bits hold all 24 of a float32.  With the leading powers of two
+// of x and y taken as 1, |m| <= 2^-8 and |l| <= 2^-17, so the six plane pairs
+// h h', h m', m h', m m', h l', l h' leave out at most 2^-24 of a product x y,
+// of either sign.  (Truncated planes would all carry the sign of x: |m| <
+// 2^-7, |l| < 2^-15, and up to 2^-21 of a product lost, always towards zero.)
+//
+// Range: an x that is infinite, or rounds to infinity, gives NaN in the lower
+// planes (inf - inf), and below 2^-110 the last plane runs out of bf16's
+// range (2^-133 is its smallest number), so that a kernel either recomputes in
+// float32 the results that planes_unsure() names, or splits 2^16 x (SCALED),
+// which keeps the last bit of every float32 and moves the upper end to 2^112;
+// it then takes the scales off its sums and recomputes what is not finite.
+// (The scale is one more instruction per element: it pays where an operand is
+// split once for many products.)
+constexpr float kPlanesScale = 65536.f;
+template <bool SCALED = false>
 __device__ __forceinline__ void split3_bf16x8(const float (&v)[8], u32x4& h, u32x4& m, u32x4& l) {
+  constexpr float S = SCALED ? kPlanesScale : 1.f;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    const uint32_t a = __float_as_uint(v[2 * p]), b = __float_as_uint(v[2 * p + 1]);
-    const float ra = v[2 * p] - __uint_as_float(a & 0xFFFF0000u);
-    const float rb = v[2 * p + 1] - __uint_as_float(b & 0xFFFF0000u);
-    const uint32_t a1 = __float_as_uint(ra), b1 = __float_as_uint(rb);
-    const float sa = ra - __uint_as_float(a1 & 0xFFFF0000u);
-    const float sb = rb - __uint_as_float(b1 & 0xFFFF0000u);
-    // the high halves of two dwords, the first in bits 0..15
-    h[p] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-    m[p] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+    const float a = v[2 * p] * S, b = v[2 * p + 1] * S;
+    h[p] = pack_bf16x2(a, b);
+    const float ra = a - lo_bf16(h[p]), rb = b - hi_bf16(h[p]);
+    m[p] = pack_bf16x2(ra, rb);
+    const float sa = ra - lo_bf16(m[p]), sb = rb - hi_bf16(m[p]);
+    // at most 8 bits are left: the high halves of two dwords, the first in
+    // bits 0..15
     l[p] = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302u);
   }
+}
+// A sum of plane products that may not be a float32 sum's: not finite, or not
+// zero and so small that operands may have lost bits (an operand below 2^-110
+// is off by 2^-133 at most: 2^-24 of a sum of 2^-80 even where the other
+// operand's absolute values add up to 2^28).  Operands below 2^-134 are zero
+// in every plane and are not noticed.
+__device__ __forceinline__ bool planes_unsure(float v) {
+  const float a = __uint_as_float(__float_as_uint(v) & 0x7FFFFFFFu);
+  return !(a < __builtin_inff()) || (a < 0x1p-80f && a != 0.f);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
