@@ -435,10 +435,12 @@ __global__ __launch_bounds__(64 * kS32Waves) void project_weights_f32_mfma(
               for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
+                  // both operands zero past k, where T may hold 0 x infinity
                   const int col = 16 * kt + 4 * g + s;
                   const float a = col < k ? U[(int64_t)(r0 + n16) * k + col] : 0.f;
 #pragma unroll
-                  for (int i = 0; i < NT; ++i) o[i] = mfma16x16x4f32(a, acc[kt][i][s], o[i]);
+                  for (int i = 0; i < NT; ++i)
+                    o[i] = mfma16x16x4f32(a, col < k ? acc[kt][i][s] : 0.f, o[i]);
                 }
               if (on) put(r0 + 4 * g, o);
             }

@@ -76,6 +76,28 @@ def test_weight_strips_propagate_non_finite(n):
     check_elementwise("same strip", got[:, near], O.project_weights(Wh[:, near], Uh), M, L, False, False)
 
 
+# widths that fill no tile, both widths of strips and both passes' chunk sizes;
+# a basis of one sign, so that an infinity gives infinities and not NaN
+@pytest.mark.parametrize("n", [66004, 20036, 260])
+@pytest.mark.parametrize("k", [1, 3, 16, 33, 51, 101])
+def test_weight_strips_infinities_at_any_width(k, n):
+    d = 160
+    r = np.random.default_rng(k)
+    Uh = ((0.1 + r.random((d, k))) / d ** 0.5).astype(np.float32)
+    Wh = I.weights_host(d, n, 4, "f32")
+    js = [7, 130, 199, n - 1]
+    for j, v in zip(js, (np.inf, -np.inf, np.nan, np.inf)):
+        Wh[j % d, j] = v
+    W = dev(Wh)
+    ssn.project_weights(W, dev(Uh))
+    got = I.to_host(W)[:, js]
+    with np.errstate(invalid="ignore"):
+        ref = Uh.astype(np.float64) @ (Uh.T.astype(np.float64) @ Wh[:, js].astype(np.float64))
+    assert np.isinf(ref).sum() == 3 * d
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+
+
 @pytest.mark.parametrize("N,din,k", [(1, 64, 3), (33, 20036, 51), (95, 10004, 64), (160, 5012, 16),
                                      (1000, 260, 40), (70, 40052, 100), (129, 10004, 128),
                                      (257, 260, 80)])
