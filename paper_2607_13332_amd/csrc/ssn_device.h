@@ -81,9 +81,7 @@ __device__ __forceinline__ void split_bf16x8(const float* v, u32x4& hi, u32x4& l
 // range (2^-133 is its smallest number), so that a kernel either recomputes in
 // float32 the results that planes_unsure() names, or splits 2^16 x (SCALED),
 // which keeps the last bit of every float32 and moves the upper end to 2^112;
-// it then takes the scales off its sums and recomputes what is not finite.
-// (The scale is one more instruction per element: it pays where an operand is
-// split once for many products.)
+// it then takes the scale off its sums and recomputes what is not finite.
 constexpr float kPlanesScale = 65536.f;
 template <bool SCALED = false>
 __device__ __forceinline__ void split3_bf16x8(const float (&v)[8], u32x4& h, u32x4& m, u32x4& l) {
