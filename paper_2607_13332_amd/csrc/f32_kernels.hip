@@ -5,11 +5,12 @@
 // The kernels walk d in 64-wide chunks (256 contiguous bytes of a float32
 // row).  With many tokens a block stages a chunk's 64 rows of U [d, ku] (any
 // ku <= 128) once, split into three bf16 planes, double buffered, one barrier
-// per chunk.  With few tokens the waves of a block split d: each stages its
-// own chunk into a row-major float32 tile K = 16 ceil(ku / 16) wide (pitch K
-// + 4 floats, zero past ku) with no barrier and multiplies with
-// v_mfma_f32_16x16x4_f32 (the split into planes would cost a wave more than
-// the multiplications of its 16 tokens save).
+// per chunk, or (compress_f32_blocks: some widths and token counts) as it is.
+// With few tokens the waves of a block split d: each stages its own chunk into
+// a row-major float32 tile K = 16 ceil(ku / 16) wide (pitch K + 4 floats, zero
+// past ku) with no barrier and multiplies with v_mfma_f32_16x16x4_f32 (the
+// split into planes would cost a wave more than the multiplications of its 16
+// tokens save).
 #include "ssn_device.h"
 #include "ssn_launch.h"
 
@@ -106,21 +107,43 @@ struct UStage {
   }
 };
 
+// The KP contiguous floats of a staged row that one (q, s) of the float32
+// kernels multiplies by (16-byte aligned for KP % 4 == 0, 8-byte for KP % 2).
+template <int KP>
+__device__ __forceinline__ void u_row(const float* ur, float (&b)[KP]) {
+  if constexpr (KP % 4 == 0) {
+#pragma unroll
+    for (int h = 0; h < KP; h += 4) {
+      const f32x4 v = *(const f32x4*)(ur + h);
+      b[h] = v[0]; b[h + 1] = v[1]; b[h + 2] = v[2]; b[h + 3] = v[3];
+    }
+  } else if constexpr (KP % 2 == 0) {
+#pragma unroll
+    for (int h = 0; h < KP; h += 2) {
+      const f32x2 v = *(const f32x2*)(ur + h);
+      b[h] = v[0]; b[h + 1] = v[1];
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < KP; ++h) b[h] = ur[h];
+  }
+}
+
 // ===========================================================================
 // compress / gradient projection, Z [N, kz] = (X - E[ids]) U (or X U, minus
 // P[ids] with the projected table), on the bf16 matrix cores: D = X - E
 // (formed in registers, one float32 rounding) and U are split exactly into
 // three bf16 planes and a product takes the six plane pairs that leave out at
-// most 2^-24 of it, in 96 cycles of the matrix core for 32 columns of d where the
-// float32 instruction takes 256; the five small pairs are summed apart and
-// added once at the end.
+// most 2^-24 of it, in 96 cycles of the matrix core for 32 columns of d where
+// the float32 instruction takes 256; the five small pairs are summed apart
+// and added once at the end.
 //
 // Block = W waves x 16 tokens, every wave sweeping all of d (start rotated
 // per block) in chunks of 64.  U's planes are staged per block in B-operand
 // order, double buffered, one barrier per chunk; a staging task is 8 rows of
 // one column (columns past ku repeat the last one: their coordinates are not
-// stored).  Rows of X and E arrive 4 rows x 256 contiguous bytes per
-// instruction, one chunk ahead, and D changes lanes through a wave-private
+// stored), its loads UA chunks ahead of its use.  Rows of X and E arrive 4
+// rows x 256 contiguous bytes per instruction, one chunk ahead, and D changes lanes through a wave-private
 // XOR-swizzled LDS tile; the wave splits its A operands as it reads them.
 // Bound: HBM.  Measured against the float32 instructions, projection /
 // compress: N = 32768, d = 4096, k = 64 167 / 204 -> 133 / 184 us (5.8 TB/s
@@ -131,7 +154,7 @@ struct UStage {
 // infinity or NaN, an overflow, a result below 2^-80) sweeps d again with
 // float32 instructions straight from memory.
 // ===========================================================================
-template <int KP, bool HAS_E, bool HAS_P, int W>
+template <int KP, bool HAS_E, bool HAS_P, int W, int UA>
 __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
     const float* __restrict__ X, const int32_t* __restrict__ ids, const float* __restrict__ E,
     const float* __restrict__ U, float* __restrict__ Z, int64_t N, int d, int64_t V,
@@ -175,22 +198,23 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
   };
   // U: task q is column q % K of the 8 rows q / K of the chunk (threads past
   // the last task repeat it and do not store)
-  float ur[TPT][8];
-  auto load_u = [&](int c) {
+  static_assert(UA == 1 || UA == 2, "chunks that U runs ahead of its use");
+  float ur[UA][TPT][8];
+  auto load_u = [&](int c, float(&uo)[TPT][8]) {
 #pragma unroll
     for (int i = 0; i < TPT; ++i) {
       const int q = NTASK % T == 0 ? tid + T * i : min(tid + T * i, NTASK - 1);
       const float* src = U + (int64_t)(c * DC + 8 * (q / K)) * ku + min(q % K, ku - 1);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ur[i][e] = src[e * ku];
+      for (int e = 0; e < 8; ++e) uo[i][e] = src[e * ku];
     }
   };
-  auto store_u = [&](int buf) {
+  auto store_u = [&](int buf, const float(&uo)[TPT][8]) {
 #pragma unroll
     for (int i = 0; i < TPT; ++i) {
       const int q = tid + T * i, col = q % K, rg = q / K;
       u32x4 h, m, l;
-      split3_bf16x8(ur[i], h, m, l);
+      split3_bf16x8(uo[i], h, m, l);
       if (NTASK % T == 0 || q < NTASK) {
         u32x4* dst = ut[buf] + ((rg >> 2) * KP + (col >> 4)) * 192 + 16 * (rg & 3) + (col & 15);
         dst[0] = h;
@@ -212,7 +236,8 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
 #pragma unroll
   for (int i = 0; i < KP; ++i) acc[i] = sm[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // chunk i, i % 2 == B: its U already staged, its rows in set B
+  // chunk i, i % 2 == B: its U already staged, its rows in set B; with UA == 2
+  // chunk i + 1's U on its way to register set B ^ 1
   auto body = [&](int i, auto Bc) {
     constexpr int B = decltype(Bc)::value;
     // park chunk i's rows of D
@@ -221,7 +246,7 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
       const int r = 4 * m + g;
       dw[r * 16 + (n16 ^ r)] = HAS_E ? xs[B][m] - es[B][m] : xs[B][m];
     }
-    load_u(chunk(last(i + 1)));
+    load_u(chunk(last(i + UA)), ur[B % UA]);
     load_rows(chunk(last(i + 2)), xs[B], es[B]);
     __syncthreads();
 #pragma unroll
@@ -243,13 +268,14 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
         sm[p] = mfma16x16x32(h, um, sm[p]);
       }
     }
-    store_u(B ^ 1);
+    store_u(B ^ 1, ur[(B ^ 1) % UA]);
   };
 
-  load_u(chunk(0));
+  load_u(chunk(0), ur[0]);
   load_rows(chunk(0), xs[0], es[0]);
+  if constexpr (UA == 2) load_u(chunk(last(1)), ur[1]);
   load_rows(chunk(last(1)), xs[1], es[1]);
-  store_u(0);
+  store_u(0, ur[0]);
   int i = 0;
   for (; i + 1 < nch; i += 2) {
     body(i, std::integral_constant<int, 0>{});
@@ -300,7 +326,136 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
 }
 
 // ===========================================================================
-// compress / gradient projection for few tokens (the kernel above runs
+// The same with float32 MFMAs: U's rows go to LDS as they are, in 16-byte
+// pieces where the basis fills its tiles (ku = 16 KP, else SPAN), so that the
+// block spends nothing on splitting them, which with one 64-token block per
+// compute unit takes longer than the multiplications it saves.  C = D [16 tokens x
+// 4] . U [4 x 16]: MFMA (q, s) pairs K slot g with d = 16 q + 4 g + s, a lane's
+// A values for s = 0..3 are one 16-byte read of its token's row of D from the
+// wave-private tile it was parked in.  Column slot j of tile i is coordinate
+// KP j + i, so the B values of all KP tiles for one (q, s) are the KP
+// contiguous floats U[16 q + 4 g + s][KP j ..] of the staged tile, and lane
+// (j, g) ends with coordinates KP j .. KP j + KP - 1 of tokens 4 g .. 4 g + 3.
+// Block = W waves x 16 tokens, every wave sweeping all of d (start rotated per
+// block).
+// ===========================================================================
+template <int KP, bool HAS_E, bool HAS_P, bool SPAN, int W>
+__global__ __launch_bounds__(64 * W) void compress_f32_blocks(
+    const float* __restrict__ X, const int32_t* __restrict__ ids, const float* __restrict__ E,
+    const float* __restrict__ U, float* __restrict__ Z, int64_t N, int d, int64_t V,
+    const float* __restrict__ Pt, uint16_t* __restrict__ Zb, int kz, int ku) {
+  static_assert(!(HAS_E && HAS_P), "the embedding is subtracted as rows or as projected rows");
+  constexpr int K = 16 * KP, DC = kF32Chunk;
+  using Stage = UStage<K, 64 * W, SPAN>;
+  constexpr int UP = Stage::UP, FPT = Stage::FPT;
+  __shared__ __align__(16) float ut[2][DC * UP];
+  __shared__ f32x4 dt[W][16 * 16];                 // [wave][token * 16 + (cell ^ token)]
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n16 = lane & 15, g = lane >> 4;
+  const int64_t tok0 = (int64_t)blockIdx.x * (16 * W) + 16 * wave;
+  // HAS_P: table row offsets of the epilogue's tokens 4 g + r, looked up now
+  int64_t prow[HAS_P ? 4 : 1];
+  if constexpr (HAS_P) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t t = tok0 + 4 * g + r;
+      prow[r] = t < N ? clamp_id(ids[t], V) * kz : 0;
+    }
+  }
+
+  // rows: instruction m covers tokens 4 m .. 4 m + 3, 16 lanes (256 bytes) each
+  const float* xrow[4];
+  const float* erow[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    int64_t t = tok0 + 4 * m + g;
+    t = t < N ? t : N - 1;
+    xrow[m] = X + t * d + 4 * n16;
+    erow[m] = HAS_E ? E + clamp_id(ids[t], V) * d + 4 * n16 : nullptr;
+  }
+  const Stage stage(tid, ku);
+  stage.zero_pad(&ut[0][0], 2);
+  f32x4 ust[2][FPT];
+  f32x4 xs[2][4], es[2][4];
+  auto load_rows = [&](int c, f32x4(&xo)[4], f32x4(&eo)[4]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      xo[m] = __builtin_nontemporal_load((const f32x4*)(xrow[m] + c * DC));
+      if constexpr (HAS_E) eo[m] = *(const f32x4*)(erow[m] + c * DC);
+    }
+  };
+
+  const int nch = d / DC;
+  const int rot = (int)(blockIdx.x % (unsigned)nch);
+  auto chunk = [&](int i) {
+    const int x = i + rot;
+    return x < nch ? x : x - nch;
+  };
+  auto last = [&](int i) { return i < nch ? i : nch - 1; };
+  f32x4* dw = dt[wave];
+  f32x4 acc[KP];
+#pragma unroll
+  for (int i = 0; i < KP; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  auto body = [&](int i, auto Bc) {
+    constexpr int B = decltype(Bc)::value;
+    stage.load(U, chunk(last(i + 2)), ust[B]);
+    load_rows(chunk(last(i + 1)), xs[B ^ 1], es[B ^ 1]);
+    // park chunk i's rows of D
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int r = 4 * m + g;
+      dw[r * 16 + (n16 ^ r)] = HAS_E ? xs[B][m] - es[B][m] : xs[B][m];
+    }
+    __syncthreads();
+    const float* ub = ut[B];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 a = dw[n16 * 16 + ((4 * q + g) ^ n16)];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        float b[KP];
+        u_row<KP>(ub + (16 * q + 4 * g + s) * UP + KP * n16, b);
+#pragma unroll
+        for (int h = 0; h < KP; ++h) acc[h] = mfma16x16x4f32(a[s], b[h], acc[h]);
+      }
+    }
+    stage.store(ut[B ^ 1], ust[B ^ 1]);
+  };
+
+  stage.load(U, chunk(0), ust[0]);
+  load_rows(chunk(0), xs[0], es[0]);
+  stage.load(U, chunk(last(1)), ust[1]);
+  stage.store(ut[0], ust[0]);
+  int i = 0;
+  for (; i + 1 < nch; i += 2) {
+    body(i, std::integral_constant<int, 0>{});
+    body(i + 1, std::integral_constant<int, 1>{});
+  }
+  if (i < nch) body(i, std::integral_constant<int, 0>{});
+
+  // lane (j, g): coordinates KP j + h of tokens 4 g + r
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t t = tok0 + 4 * g + r;
+    if (t >= N) continue;
+#pragma unroll
+    for (int h = 0; h < KP; ++h) {
+      const int col = KP * n16 + h;
+      if (col >= kz) continue;
+      float v = acc[h][r];
+      if constexpr (HAS_P) v -= Pt[prow[r] + col];
+      if (Zb)
+        Zb[t * kz + col] = (uint16_t)f32_to_bf16(v);
+      else
+        Z[t * kz + col] = v;
+    }
+  }
+}
+
+// ===========================================================================
+// compress / gradient projection for few tokens (the kernels above run
 // N / 64 blocks, a fraction of the chip).  Block = 16 tokens x PW waves; wave
 // w walks the w-th of PW equal ranges of d with a wave-private U tile and
 // its A operands read straight from the rows, so no barrier is needed until
@@ -373,24 +528,8 @@ __global__ __launch_bounds__(64 * PW) void compress_f32_split(
       const f32x4 a = HAS_E ? xs[B][q] - es[B][q] : xs[B][q];
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const float* ur = ub + (16 * q + 4 * g + s) * UP + KP * n16;
         float b[KP];
-        if constexpr (KP % 4 == 0) {
-#pragma unroll
-          for (int h = 0; h < KP; h += 4) {
-            const f32x4 v = *(const f32x4*)(ur + h);
-            b[h] = v[0]; b[h + 1] = v[1]; b[h + 2] = v[2]; b[h + 3] = v[3];
-          }
-        } else if constexpr (KP % 2 == 0) {
-#pragma unroll
-          for (int h = 0; h < KP; h += 2) {
-            const f32x2 v = *(const f32x2*)(ur + h);
-            b[h] = v[0]; b[h + 1] = v[1];
-          }
-        } else {
-#pragma unroll
-          for (int h = 0; h < KP; ++h) b[h] = ur[h];
-        }
+        u_row<KP>(ub + (16 * q + 4 * g + s) * UP + KP * n16, b);
 #pragma unroll
         for (int h = 0; h < KP; ++h) acc[h] = mfma16x16x4f32(a[s], b[h], acc[h]);
       }
@@ -448,20 +587,75 @@ __global__ __launch_bounds__(64 * PW) void compress_f32_split(
 // ===========================================================================
 // Launchers.
 // ===========================================================================
-template <int KP, int W>
-static hipError_t launch_compress_f32_kp(int64_t N, int d, int64_t V, const float* X,
-                                         const int32_t* ids, const float* E, const float* U,
-                                         float* Z, const float* P, hipStream_t st, uint16_t* Zb,
-                                         int kz, int ku) {
+template <int KP, int W, int UA>
+static hipError_t launch_compress_f32_planes(int64_t N, int d, int64_t V, const float* X,
+                                             const int32_t* ids, const float* E, const float* U,
+                                             float* Z, const float* P, hipStream_t st, uint16_t* Zb,
+                                             int kz, int ku) {
+  // U's second register set pays with one 64-token block per compute unit,
+  // where nothing else hides the wait for U's next chunk (N = 12205, d = 2048,
+  // k = 8 projection 37 -> 28 us, k = 51 50 -> 47), and for the projection
+  // beyond (N = 20000, d = 5120, k = 8 101 -> 84).  compress has the rows of
+  // E in flight too: only k <= 16 gains (N = 14000, d = 4096, k = 16 77 -> 68
+  // us; k = 32 80 -> 85), and only with one block per unit (N = 20000: 116 ->
+  // 122).
   const dim3 grid((unsigned)((N + 16 * W - 1) / (16 * W)));
-  if (E)
-    hipLaunchKernelGGL((compress_f32_mfma<KP, true, false, W>), grid, dim3(64 * W), 0, st, X, ids,
+  if (E) {
+    if constexpr (KP == 1 && UA == 2) {
+      if ((int64_t)grid.x <= device_cu_count()) {
+        hipLaunchKernelGGL((compress_f32_mfma<KP, true, false, W, 2>), grid, dim3(64 * W), 0, st, X, ids,
+                           E, U, Z, N, d, V, P, Zb, kz, ku);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((compress_f32_mfma<KP, true, false, W, 1>), grid, dim3(64 * W), 0, st, X, ids,
                        E, U, Z, N, d, V, P, Zb, kz, ku);
-  else if (P)
-    hipLaunchKernelGGL((compress_f32_mfma<KP, false, true, W>), grid, dim3(64 * W), 0, st, X, ids,
+  } else if (P) {
+    hipLaunchKernelGGL((compress_f32_mfma<KP, false, true, W, UA>), grid, dim3(64 * W), 0, st, X, ids,
                        E, U, Z, N, d, V, P, Zb, kz, ku);
+  } else {
+    hipLaunchKernelGGL((compress_f32_mfma<KP, false, false, W, UA>), grid, dim3(64 * W), 0, st, X,
+                       ids, E, U, Z, N, d, V, P, Zb, kz, ku);
+  }
+  return hipGetLastError();
+}
+
+// Where compress_f32_blocks runs (64-token blocks).  k <= 16 and up to 1024
+// tokens, where a few blocks wait for their loads and little else (N = 512, d =
+// 256, k = 8 projection 5.9 / 5.4 us, compress 6.5 / 6.0; N = 1500, d = 576
+// 9.8 / 11.3).  With a basis as wide as its tiles: the projection with up to one block per compute unit and k <= 80 (N
+// = 16384, d = 4096, planes against this: k = 16 58.9 / 46.2 us, 64 94 / 86; d =
+// 576, k = 80, N = 4096 21.5 / 18.4; k = 96 129 / 130 on both), or more blocks
+// and k <= 32 (N = 20000, d = 5120, k = 16 87 / 79; k = 64 158 / 180); compress
+// with more blocks and k <= 32 (N = 20000, d = 4096, k = 16 116 / 114, k = 32
+// 127 / 124; k = 64 145 / 177).
+template <int KP>
+static bool compress_f32_uses_blocks(int64_t N, bool has_e, int kz, int ku) {
+  if (KP == 1 && N <= 1024) return true;
+  if (ku != 16 * KP || kz != ku) return false;
+  const bool one = (N + 63) / 64 <= device_cu_count();
+  return has_e ? KP <= 2 && !one : KP <= 2 || (KP <= 5 && one);
+}
+
+template <int KP, bool SPAN>
+static hipError_t launch_compress_f32_blocks(int64_t N, int d, int64_t V, const float* X,
+                                             const int32_t* ids, const float* E, const float* U,
+                                             float* Z, const float* P, hipStream_t st, uint16_t* Zb,
+                                             int kz, int ku) {
+  constexpr int W = 4;
+  const dim3 grid((unsigned)((N + 16 * W - 1) / (16 * W)));
+  if constexpr (KP <= 2) {
+    if (E) {
+      hipLaunchKernelGGL((compress_f32_blocks<KP, true, false, SPAN, W>), grid, dim3(64 * W), 0, st, X,
+                         ids, E, U, Z, N, d, V, P, Zb, kz, ku);
+      return hipGetLastError();
+    }
+  }
+  if (P)
+    hipLaunchKernelGGL((compress_f32_blocks<KP, false, true, SPAN, W>), grid, dim3(64 * W), 0, st, X,
+                       ids, E, U, Z, N, d, V, P, Zb, kz, ku);
   else
-    hipLaunchKernelGGL((compress_f32_mfma<KP, false, false, W>), grid, dim3(64 * W), 0, st, X,
+    hipLaunchKernelGGL((compress_f32_blocks<KP, false, false, SPAN, W>), grid, dim3(64 * W), 0, st, X,
                        ids, E, U, Z, N, d, V, P, Zb, kz, ku);
   return hipGetLastError();
 }
@@ -501,8 +695,16 @@ static hipError_t launch_compress_f32_w(int64_t N, int d, int64_t V, const float
   if (8 * ((N + 63) / 64) <= 5 * cus && d % ((KP <= 4 ? 8 : 4) * kF32Chunk) == 0)
     return span ? launch_compress_f32_split<KP, true>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku)
                 : launch_compress_f32_split<KP, false>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
-  return eight ? launch_compress_f32_kp<KP, 8>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku)
-               : launch_compress_f32_kp<KP, 4>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
+  if (eight) return launch_compress_f32_planes<KP, 8, 1>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
+  if constexpr (KP <= 5) {
+    if (compress_f32_uses_blocks<KP>(N, E != nullptr, kz, ku)) {
+      if constexpr (KP == 1) {
+        if (span) return launch_compress_f32_blocks<KP, true>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
+      }
+      return launch_compress_f32_blocks<KP, false>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
+    }
+  }
+  return launch_compress_f32_planes<KP, 4, 2>(N, d, V, X, ids, E, U, Z, P, st, Zb, kz, ku);
 }
 
 hipError_t launch_compress_f32(int64_t N, int64_t d, int64_t k, int64_t V, const float* X,

@@ -49,6 +49,15 @@ def test_many_token_compress(N, d, k):
         assert torch.equal(ssn.project_grad(X, ssn.pad_basis(U), k=k), ssn.project_grad(X, U))
 
 
+# 64-token blocks with float32 instructions (widths of whole tiles, or up to
+# 16): one token, edges of a block, one block per compute unit and one more,
+# and the last widths of each line
+@pytest.mark.parametrize("N,d,k", [(1, 64, 16), (1, 192, 1), (65, 320, 9), (1024, 64, 15), (1025, 64, 15), (63, 192, 32), (65, 320, 48), (12300, 128, 80),
+                                   (16384, 64, 64), (16385, 64, 32), (16400, 128, 16), (16385, 64, 48)])
+def test_float32_blocks(N, d, k):
+    test_many_token_compress(N, d, k)
+
+
 def test_many_token_infinities_propagate():
     N, d, k = 33000, 128, 33
     U = I.to_device(I.store(I.gaussian_orthonormal_basis(d, k, 3), "f32"), "f32", DEV)
