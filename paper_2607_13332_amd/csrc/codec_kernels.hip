@@ -1313,7 +1313,7 @@ hipError_t launch_project_ranges(int dtype, int64_t N, int64_t d, int64_t k, con
 // fills at least 90 % of the blocks' last round, else the smallest that
 // reaches one block per unit (N = 12288, d = 5120, k = 51: 96 blocks in 5
 // ranges 57.9 us, in 4 ranges 64.3 us).
-static int decompress_grid_split(int64_t blocks, int chunks) {
+int decompress_grid_split(int64_t blocks, int chunks) {
   const int64_t cus = device_cu_count();
   int gy = 1;
   if (blocks < cus) {
@@ -1330,6 +1330,12 @@ static int decompress_grid_split(int64_t blocks, int chunks) {
     if (gy == 1) gy = first > 0 ? first : 1;
   }
   return gy;
+}
+
+bool decompress_chunks_fill(int64_t N, int64_t d) {
+  const int64_t cus = device_cu_count(), blocks = (N + 127) / 128;
+  const int64_t grid = blocks * decompress_grid_split(blocks, (int)(d / kDecompressDC));
+  return grid <= cus && 10 * grid >= 9 * cus;
 }
 
 template <int KS2, bool HAS_E, int KM>

@@ -303,7 +303,11 @@ __global__ __launch_bounds__(64 * kExp32Waves, 2) void decompress_cols_f32(
 }
 
 // Two blocks per compute unit (two waves per SIMD), each with an equal range
-// of the 16-token tiles.
+// of the 16-token tiles; one block per unit where two would have about one
+// tile each, so that half the blocks fetch and split U (N = 2048, d = 1024, k
+// = 48 expansion 98 -> 85 hundredths of the time of float32 instructions, N =
+// 1500, d = 576 97 -> 86; with two tiles each it loses, N = 4096, d = 1024 84
+// -> 85, decompress 91 -> 98).
 template <int KS, bool HAS_E, bool GZ, bool ZB>
 static hipError_t launch_cols(int64_t N, int d, int k, int64_t V, const float* Zc, const uint16_t* Zb,
                               const int32_t* ids, const float* E, const float* U, float* Y, int kz,
@@ -311,6 +315,7 @@ static hipError_t launch_cols(int64_t N, int d, int k, int64_t V, const float* Z
   constexpr int BC = kExp32Waves * 16 * exp32_tiles(KS);
   const int64_t tiles = (N + 15) / 16, nd = ((int64_t)d + BC - 1) / BC;
   int64_t ranges = 2 * (int64_t)device_cu_count() / nd;
+  if (4 * tiles <= 5 * ranges) ranges /= 2;
   ranges = ranges < 1 ? 1 : (ranges < tiles ? ranges : tiles);
   hipLaunchKernelGGL((decompress_cols_f32<KS, HAS_E, GZ, ZB>), dim3((unsigned)(nd * ranges)),
                      dim3(64 * kExp32Waves), 0, st, Zc, Zb, ids, E, U, Y, N, d, k, V, kz, (int)nd,
@@ -330,10 +335,33 @@ static hipError_t launch_cols_ks(int64_t N, int d, int k, int64_t V, const float
             : launch_cols<KS, false, false, false>(N, d, k, V, Zc, Zb, ids, E, U, Y, kz, st);
 }
 
+// Where float32 instructions on U as it is stored (decompress_f32_chunks) beat
+// planes in registers: few coordinates, and fewer output elements than pay
+// for a wave's start.  Measured in us, chunks against columns, with E / without:
+//   k = 8:  N = 512, d = 256 4.3 / 5.3 and 4.1 / 4.7; N = 4096, d = 1024 7.6 /
+//           9.5 and 5.8 / 7.0; N = 3000, d = 2048 100 : 110 and 100 : 111
+//           (relative); N = 3000, d = 4096 100 : 104 and 100 : 88
+//   k = 24: N = 3000, d = 576 100 : 131 and 100 : 111; N = 1500, d = 2048 100 :
+//           100 and 120 : 100
+// and further where their grid is one full round of blocks (N = 4096, 8192):
+//   k = 8:  N = 8192, d = 2048 100 : 108 and 100 : 92; N = 2048, d = 5120 100 :
+//           123 and 100 : 115; a stage's step at N = 5000, d = 5120, no full
+//           round, 178 / 168
+//   k = 24: N = 2048, d = 5120 with E 100 : 110, without 100 : 98.
+static bool decompress_f32_uses_chunks(int64_t N, int64_t d, int64_t ku, bool has_e) {
+  const int64_t out = N * d;
+  if (ku >= 32) return false;
+  if (out <= (int64_t)1 << (ku <= 16 ? 23 : 21)) return true;
+  if (!has_e && (ku > 16 || out > 5 * ((int64_t)1 << 21))) return false;
+  return out < (int64_t)1 << 25 && decompress_chunks_fill(N, d);
+}
+
 hipError_t launch_decompress_f32(int64_t N, int64_t d, int64_t k, int64_t V, const float* Z,
                                  const int32_t* ids, const float* E, const float* U, float* Y,
                                  bool gather_z, hipStream_t st, const uint16_t* Zb, int kz) {
   const int dd = (int)d, ku = (int)k;
+  if (decompress_f32_uses_chunks(N, d, k, E != nullptr))
+    return launch_decompress_f32_chunks(N, dd, V, Z, ids, E, U, Y, gather_z, st, Zb, kz, ku);
   switch ((kz + 31) / 32) {
     case 1: return launch_cols_ks<1>(N, dd, ku, V, Z, Zb, ids, E, U, Y, gather_z, kz, st);
     case 2: return launch_cols_ks<2>(N, dd, ku, V, Z, Zb, ids, E, U, Y, gather_z, kz, st);

@@ -1,6 +1,7 @@
 // Stage-boundary compress / gradient projection with float32 storage on the
-// matrix cores.  Paper: section 4.1, Eq. (2) -- Z = (X - E[ids]) U; the
-// gradient form is the same kernels without the embedding.
+// matrix cores, and decompress / expansion for narrow bases.  Paper: section
+// 4.1, Eq. (2) -- Z = (X - E[ids]) U; the gradient form is the same kernels
+// without the embedding.
 //
 // The kernels walk d in 64-wide chunks (256 contiguous bytes of a float32
 // row).  With many tokens a block stages a chunk's 64 rows of U [d, ku] (any
@@ -582,6 +583,159 @@ __global__ __launch_bounds__(64 * PW) void compress_f32_split(
         Z[t * kz + col] = v;
     }
   }
+}
+
+// ===========================================================================
+// decompress / gradient expansion with float32 MFMAs, for bases of up to 31
+// columns where the column kernel (decompress_f32.hip) loses: there a wave
+// splits 64 rows of U into planes before its first tile, which with few
+// tokens takes longer than the tiles.  Output tiles are computed transposed,
+// Y^T [16 d x 16 tokens] = U_rows [16 d x 4] . Z^T [4 x 16 tokens]; MFMA
+// (q, s) pairs K slot g with coordinate 16 q + 4 g + s, so a lane's A values
+// for s = 0..3 are one 16-byte LDS read of a U row and its B values four
+// coordinates of its token, held in registers for the whole kernel.  Lane
+// (token n16, g) then holds d = 16 tt + 4 g .. + 3 of its token for tile tt:
+// parked in a wave-private XOR-swizzled LDS tile, read back as row pieces,
+// E[ids] added (loaded one chunk ahead), stored non-temporally.  Block = 8
+// waves x 16 tokens; a second grid dimension splits d
+// (decompress_grid_split).  Tokens past N recompute token N - 1 and store the
+// same bytes there.  GZ: the coordinate row of token t is Z[ids[t]].
+// ===========================================================================
+template <int KQ, bool HAS_E, bool GZ, bool SPAN>
+__global__ __launch_bounds__(512) void decompress_f32_chunks(
+    const float* __restrict__ Zc, const int32_t* __restrict__ ids, const float* __restrict__ E,
+    const float* __restrict__ U, float* __restrict__ Y, int64_t N, int d, int64_t V,
+    const uint16_t* __restrict__ Zb, int kz, int ku) {
+  static_assert(!(HAS_E && GZ), "gathered coordinates carry no additive embedding");
+  constexpr int K = 16 * KQ, DC = kF32Chunk, W = 8;
+  using Stage = UStage<K, 64 * W, SPAN>;
+  constexpr int UP = Stage::UP, FPT = Stage::FPT;
+  __shared__ __align__(16) float ut[2][DC * UP];
+  __shared__ f32x4 st[W][16 * 16];                 // [wave][token * 16 + (cell ^ token)]
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n16 = lane & 15, g = lane >> 4;
+  const int64_t tok0 = (int64_t)blockIdx.x * (16 * W) + 16 * wave;
+
+  // B operand: coordinates 16 q + 4 g + s of token n16 (zero past kz)
+  float zf[KQ][4];
+  {
+    int64_t t = tok0 + n16;
+    t = t < N ? t : N - 1;
+    const int64_t zrow = (GZ ? clamp_id(ids[t], V) : t) * (int64_t)kz;
+#pragma unroll
+    for (int q = 0; q < KQ; ++q)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int c = 16 * q + 4 * g + s;
+        zf[q][s] = c < kz ? (Zb ? bf16_to_f32(Zb[zrow + c]) : Zc[zrow + c]) : 0.f;
+      }
+  }
+  // epilogue rows: instruction m covers tokens 4 m .. 4 m + 3, 16 lanes each
+  float* yrow[4];
+  const float* erow[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    int64_t t = tok0 + 4 * m + g;
+    t = t < N ? t : N - 1;
+    yrow[m] = Y + t * d + 4 * n16;
+    erow[m] = HAS_E ? E + clamp_id(ids[t], V) * d + 4 * n16 : nullptr;
+  }
+  const Stage stage(tid, ku);
+  stage.zero_pad(&ut[0][0], 2);
+  f32x4 ust[2][FPT];
+  f32x4 ering[2][4];
+  auto load_e = [&](int c, f32x4(&eo)[4]) {
+    if constexpr (HAS_E) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) eo[m] = *(const f32x4*)(erow[m] + c * DC);
+    }
+  };
+
+  const int nch = d / (DC * (int)gridDim.y);
+  const int pbase = (int)blockIdx.y * nch;
+  const int rot = (int)(blockIdx.x % (unsigned)nch);
+  auto chunk = [&](int i) {
+    const int x = i + rot;
+    return pbase + (x < nch ? x : x - nch);
+  };
+  auto last = [&](int i) { return i < nch ? i : nch - 1; };
+  f32x4* sw = st[wave];
+
+  // chunk i, i % 2 == B: loads for later chunks, barrier, MFMAs, epilogue,
+  // then the LDS store of chunk i + 1's U (loaded one chunk earlier)
+  auto body = [&](int i, auto Bc) {
+    constexpr int B = decltype(Bc)::value;
+    const int c = chunk(i);
+    stage.load(U, chunk(last(i + 2)), ust[B]);
+    load_e(chunk(last(i + 1)), ering[B ^ 1]);
+    __syncthreads();
+    const float* ub = ut[B];
+    f32x4 acc[4];
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt) acc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < KQ; ++q)
+#pragma unroll
+      for (int tt = 0; tt < 4; ++tt) {
+        const f32x4 a = *(const f32x4*)(ub + (16 * tt + n16) * UP + 16 * q + 4 * g);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[tt] = mfma16x16x4f32(a[s], zf[q][s], acc[tt]);
+      }
+    wave_lds_fence();
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt) sw[n16 * 16 + ((4 * tt + g) ^ n16)] = acc[tt];
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int r = 4 * m + g;
+      f32x4 v = sw[r * 16 + (n16 ^ r)];
+      if constexpr (HAS_E) v += ering[B][m];
+      __builtin_nontemporal_store(v, (f32x4*)(yrow[m] + c * DC));
+    }
+    stage.store(ut[B ^ 1], ust[B ^ 1]);
+  };
+
+  stage.load(U, chunk(0), ust[0]);
+  stage.load(U, chunk(last(1)), ust[1]);
+  load_e(chunk(0), ering[0]);
+  stage.store(ut[0], ust[0]);
+  int i = 0;
+  for (; i + 1 < nch; i += 2) {
+    body(i, std::integral_constant<int, 0>{});
+    body(i + 1, std::integral_constant<int, 1>{});
+  }
+  if (i < nch) body(i, std::integral_constant<int, 0>{});
+}
+
+template <int KQ, bool SPAN>
+static hipError_t launch_decompress_chunks_kq(int64_t N, int d, int64_t V, const float* Z,
+                                              const int32_t* ids, const float* E, const float* U,
+                                              float* Y, bool gather_z, hipStream_t st,
+                                              const uint16_t* Zb, int kz, int ku) {
+  const int64_t blocks = (N + 127) / 128;
+  const dim3 grid((unsigned)blocks, (unsigned)decompress_grid_split(blocks, d / kF32Chunk));
+  if (E)
+    hipLaunchKernelGGL((decompress_f32_chunks<KQ, true, false, SPAN>), grid, dim3(512), 0, st, Z, ids,
+                       E, U, Y, N, d, V, Zb, kz, ku);
+  else if (gather_z)
+    hipLaunchKernelGGL((decompress_f32_chunks<KQ, false, true, SPAN>), grid, dim3(512), 0, st, Z, ids,
+                       E, U, Y, N, d, V, Zb, kz, ku);
+  else
+    hipLaunchKernelGGL((decompress_f32_chunks<KQ, false, false, SPAN>), grid, dim3(512), 0, st, Z, ids,
+                       E, U, Y, N, d, V, Zb, kz, ku);
+  return hipGetLastError();
+}
+
+hipError_t launch_decompress_f32_chunks(int64_t N, int d, int64_t V, const float* Z,
+                                        const int32_t* ids, const float* E, const float* U, float* Y,
+                                        bool gather_z, hipStream_t st, const uint16_t* Zb, int kz,
+                                        int ku) {
+  if (ku == 16)
+    return launch_decompress_chunks_kq<1, false>(N, d, V, Z, ids, E, U, Y, gather_z, st, Zb, kz, ku);
+  if (ku < 16)
+    return launch_decompress_chunks_kq<1, true>(N, d, V, Z, ids, E, U, Y, gather_z, st, Zb, kz, ku);
+  return launch_decompress_chunks_kq<2, true>(N, d, V, Z, ids, E, U, Y, gather_z, st, Zb, kz, ku);
 }
 
 // ===========================================================================

@@ -108,6 +108,14 @@ __device__ __forceinline__ bool planes_unsure(float v) {
   return !(a < __builtin_inff()) || (a < 0x1p-80f && a != 0.f);
 }
 
+// Between a wave's writes to its private LDS tile and reads of it by other
+// lanes (and before it is overwritten): a wave's LDS operations complete in
+// order, so this only keeps the compiler from reordering them; no instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);

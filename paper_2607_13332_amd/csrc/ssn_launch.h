@@ -35,6 +35,10 @@ hipError_t launch_project_weights_f32(int count, int64_t d, const int64_t* n, in
 bool factor_grad_f32_uses_mfma(int64_t N, int64_t din, int64_t k);
 hipError_t launch_factor_grad_f32(int64_t N, int64_t din, int64_t k, const float* H, const float* GT,
                                   float* dZp, hipStream_t st);
+// Ranges of d (grid.y) for `blocks` blocks of the chunk-staged decompress
+// kernels, and whether that grid is one round of blocks, at least 90 % full.
+int decompress_grid_split(int64_t blocks, int chunks);
+bool decompress_chunks_fill(int64_t N, int64_t d);
 // bf16 form of launch_decompress (same arguments; only where
 // decompress_uses_mfma holds and Z, E, U, Y are 16-byte aligned).
 hipError_t launch_decompress_bf16(int64_t N, int64_t d, int64_t k, int64_t V, const float* Z,
@@ -45,6 +49,11 @@ hipError_t launch_decompress_bf16(int64_t N, int64_t d, int64_t k, int64_t V, co
 hipError_t launch_compress_f32(int64_t N, int64_t d, int64_t k, int64_t V, const float* X,
                                const int32_t* ids, const float* E, const float* U, float* Z,
                                const float* P, hipStream_t st, uint16_t* Zb, int kz);
+// (ku <= 31)
+hipError_t launch_decompress_f32_chunks(int64_t N, int d, int64_t V, const float* Z,
+                                        const int32_t* ids, const float* E, const float* U, float* Y,
+                                        bool gather_z, hipStream_t st, const uint16_t* Zb, int kz,
+                                        int ku);
 hipError_t launch_decompress_f32(int64_t N, int64_t d, int64_t k, int64_t V, const float* Z,
                                  const int32_t* ids, const float* E, const float* U, float* Y,
                                  bool gather_z, hipStream_t st, const uint16_t* Zb, int kz);

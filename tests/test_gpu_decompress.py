@@ -69,6 +69,17 @@ def test_decompress_shapes(N, d, k, wire, dtype):
         assert torch.equal(X0, ssn.expand_grad(T[ids.long()].contiguous(), U))
 
 
+# float32, narrow bases: both sides of the lines between the chunk-staged and
+# the column kernel (2^21, 2^23, 5 x 2^21 and 2^25 output elements, a full round
+# of blocks or not), whole and odd widths, and about one tile to a range
+@pytest.mark.parametrize("N,d,k", [(1, 128, 16), (129, 640, 31), (2048, 1024, 17), (2049, 1024, 24),
+                                   (4096, 1024, 24), (8192, 1024, 16), (8193, 1024, 8), (4096, 2560, 8),
+                                   (4224, 2560, 16), (1300, 640, 48), (1500, 640, 100)])
+@pytest.mark.parametrize("wire", ["f32", "bf16"])
+def test_float32_narrow_bases(N, d, k, wire):
+    test_decompress_shapes(N, d, k, wire, "f32")
+
+
 @pytest.mark.parametrize("N,d,k", [(200, 256, 51), (13000, 640, 33), (200, 256, 100)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_non_finite_coordinates_stay_in_their_token(N, d, k, dtype):
