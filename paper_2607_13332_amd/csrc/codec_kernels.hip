@@ -1311,8 +1311,8 @@ hipError_t launch_project_ranges(int dtype, int64_t N, int64_t d, int64_t k, con
 // 1 when the blocks alone reach one per compute unit; else the smallest
 // divisor of the chunk count that leaves every block at least two chunks and
 // fills at least 90 % of the blocks' last round, else the smallest that
-// reaches one block per unit (N = 12288, d = 5120, k = 51: 96 blocks in 5
-// ranges 57.9 us, in 4 ranges 64.3 us).
+// reaches one block per unit (96 blocks in 5 ranges of d = 5120 57.9 us, in 4
+// ranges 64.3 us).
 int decompress_grid_split(int64_t blocks, int chunks) {
   const int64_t cus = device_cu_count();
   int gy = 1;
@@ -1338,7 +1338,7 @@ bool decompress_chunks_fill(int64_t N, int64_t d) {
   return grid <= cus && 10 * grid >= 9 * cus;
 }
 
-template <int KS2, bool HAS_E, int KM>
+template <int KS2, bool HAS_E, bool GZ, int KM>
 static hipError_t launch_decompress_km(int64_t N, int d, int k, int64_t V, const float* Zc,
                                        const int32_t* ids, const void* E, const void* U, void* Y,
                                        hipStream_t st, const uint16_t* Zb, int kz) {
@@ -1348,43 +1348,73 @@ static hipError_t launch_decompress_km(int64_t N, int d, int k, int64_t V, const
   const int gy = decompress_grid_split(blocks, chunks);
   const dim3 grid((unsigned)blocks, (unsigned)gy);
   if (!HAS_E && (chunks / gy) % 2 == 0)
-    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, false, false,
+    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, GZ, false,
                                              1, 2>),
                        grid, dim3(64 * TW), 0, st, Zc, ids, (const uint16_t*)E, (const uint16_t*)U,
                        (uint16_t*)Y, N, d, k, V, Zb, kz);
   else
-    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true>), grid,
+    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, GZ>), grid,
                        dim3(64 * TW), 0, st, Zc, ids, (const uint16_t*)E, (const uint16_t*)U,
                        (uint16_t*)Y, N, d, k, V, Zb, kz);
   return hipGetLastError();
 }
 
-template <int KS2, bool HAS_E>
+template <int KS2, bool HAS_E, bool GZ>
 static hipError_t launch_chunks_ks(int64_t N, int d, int k, int64_t V, const float* Zc,
                                    const int32_t* ids, const void* E, const void* U, void* Y,
                                    hipStream_t st, const uint16_t* Zb, int kz) {
-  if (k == 32 * KS2) return launch_decompress_km<KS2, HAS_E, 0>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-  if (k % 8 == 0) return launch_decompress_km<KS2, HAS_E, 1>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
-  return launch_decompress_km<KS2, HAS_E, 2>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+  if (k == 32 * KS2) return launch_decompress_km<KS2, HAS_E, GZ, 0>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+  if constexpr (KS2 <= 2) {
+    if (k % 8 != 0) return launch_decompress_km<KS2, HAS_E, GZ, 2>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+  }
+  return launch_decompress_km<KS2, HAS_E, GZ, 1>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
 }
 
-// Where the chunk-staged kernel runs: k <= 64 and more tokens than the
-// token-split form of the column kernel takes, up to 8192.  There a block of
-// the column kernel walks only 4 to 20 tiles for the U it fetches first:
-// Pluralis-8B's step at N = 4096, d = 5120 takes 76.6 us on this kernel and
-// 78.1 on that, and the reparameterized layer at N = 4096, din = 18432 155.6
-// against 160.1; at N = 12205, d = 5120 it is 186.7 against 174.4.
-static bool decompress_uses_chunks(int64_t N, int64_t d, int64_t k) {
-  const int64_t nd = (d + 511) / 512, slots = 2 * (int64_t)device_cu_count();
-  return k <= 64 && N <= 8192 && (N + 15) / 16 > 3 * (slots / nd);
+// Where the chunk-staged kernel runs.  It spends less per block before its
+// first token (64 rows of U at a time, where a block of the column kernel
+// first takes 512 into registers), but its grid of 128-token blocks leaves a
+// ragged last round unless N suits it, and U rows that are not whole 16-byte
+// pieces (k % 8 != 0) cost it about 40 %.
+//  k <= 64: its grid is one round of blocks, at least 90 % full (N = 4096 and
+//    8192, not 5000 or 6000), past the token-split form of the column kernel
+//    (two tiles to a range).  Whole stage steps, chunks / columns in us: N =
+//    4096, d = 5120, k = 64 76.2 / 78.1, k = 32 64.5 / 66.0; N = 8192, d = 2560
+//    72.9 / 75.3; N = 4096, d = 2560 43.5 / 46.1; N = 2048, d = 5120, k = 40 51.3
+//    / 55.1; but N = 5000 113.0 / 105.8, and N = 10000, d = 4096 135 / 125.  With
+//    k % 8 != 0 only for expansions as long as an MLP's factor (layer with d_in
+//    = 18432, k = 51: N = 2048 101.9 / 104.3, N = 4096 160.4 / 162.1; stage
+//    steps at N = 4096, d = 4096 73.2 / 71.8).
+//  k > 64, whole pieces: few output elements, the fewer the wider the basis
+//    (columns / chunks, decompress: k = 72 1.23 at N = 2048, d = 4096, 0.92 at
+//    N = 12205; k = 96 1.14 at N = 2048, 0.91 at N = 6000; k = 128 1.17 at N =
+//    1024, 0.84 at N = 3000), twice as many with a full round of blocks (step
+//    at N = 2048, d = 5120, k = 96 92.0 / 87.7 us).
+//  Gathered coordinates, k <= 64: whole pieces also from 2^27 elements on, with
+//    a full round (N = 32768, d = 5120, k = 64 64.6 / 69.1 us; N = 12205 29.9 /
+//    28.5).  Otherwise as expansion, whose bits they have (with whole pieces
+//    the two kernels give the same bits).
+static bool decompress_uses_chunks(int64_t N, int64_t d, int64_t k, bool has_e, bool gather_z) {
+  const int64_t out = N * d;
+  const bool whole = k % 8 == 0;
+  if (k > 64) {
+    const int64_t most = (((int64_t)1 << 24) * 72 * 72) / (k * k);
+    return whole && out < 2 * most && (out < most || decompress_chunks_fill(N, d));
+  }
+  if (gather_z && whole && out >= (int64_t)1 << 27) return decompress_chunks_fill(N, d);
+  return N <= 8192 && (N + 15) / 16 > 2 * decompress_cols_ranges(d) && (whole || (!has_e && d > 8192)) &&
+         decompress_chunks_fill(N, d);
 }
 
-template <bool HAS_E>
+template <bool HAS_E, bool GZ>
 static hipError_t launch_chunks(int64_t N, int d, int k, int64_t V, const float* Zc,
                                 const int32_t* ids, const void* E, const void* U, void* Y,
                                 hipStream_t st, const uint16_t* Zb, int kz) {
-  return k <= 32 ? launch_chunks_ks<1, HAS_E>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz)
-                 : launch_chunks_ks<2, HAS_E>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+  switch ((k + 31) / 32) {
+    case 1: return launch_chunks_ks<1, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+    case 2: return launch_chunks_ks<2, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+    case 3: return launch_chunks_ks<3, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+    default: return launch_chunks_ks<4, HAS_E, GZ>(N, d, k, V, Zc, ids, E, U, Y, st, Zb, kz);
+  }
 }
 
 template <typename T, bool HAS_E, bool GZ>
@@ -1408,9 +1438,11 @@ hipError_t launch_decompress(int dtype, int64_t N, int64_t d, int64_t k, int64_t
     return launch_decompress_f32(N, d, k, V, Zc, ids, (const float*)E, (const float*)U, (float*)Y,
                                  gather_z, st, Zb, kz);
   if (decompress_uses_mfma(dtype, d, k) && al16(zin) && al16(U) && al16(Y) && (!has_e || al16(E))) {
-    if (!gather_z && decompress_uses_chunks(N, d, k))
-      return has_e ? launch_chunks<true>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz)
-                   : launch_chunks<false>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
+    if (decompress_uses_chunks(N, d, k, has_e, gather_z)) {
+      if (has_e) return launch_chunks<true, false>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
+      if (gather_z) return launch_chunks<false, true>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
+      return launch_chunks<false, false>(N, (int)d, (int)k, V, Zc, ids, E, U, Y, st, Zb, kz);
+    }
     return launch_decompress_bf16(N, d, k, V, Zc, ids, E, U, Y, gather_z, st, Zb, kz);
   }
   if (dtype == kF32) {

@@ -326,14 +326,22 @@ __global__ __launch_bounds__(64 * kExpandWaves, 2) void decompress_cols_bf16(
   }
 }
 
+int64_t decompress_cols_ranges(int64_t d) {
+  const int64_t r = 2 * (int64_t)device_cu_count() / ((d + kExpandBlockCols - 1) / kExpandBlockCols);
+  return r < 1 ? 1 : r;
+}
+
 // One block per slot (two blocks per compute unit: two waves per SIMD), each
-// with an equal range of the 16-token tiles.  With at most three tiles to a
+// with an equal range of the 16-token tiles.  With at most 2.75 tiles to a
 // range the waves of a block share 128 columns and split the tokens (TS), so
 // that each block fetches a quarter of the rows of U for four times the
 // tokens: N = 2048, d = 2048, k = 40 decompress 7.6 -> 6.1 us, expansion 6.6
 // -> 5.4; with more tiles 512 columns win for their longer rows and fewer
-// reads of Z (N = 4096, d = 5120: 17.9 against 19.0 us; N = 32768, d = 4096:
-// 97 against 118).  k > 64 takes the columns always (U's registers).
+// reads of Z.  Whole stage steps, TS / 512 columns in us: 2.2 tiles (N = 9000,
+// d = 1024) k = 8 34.7 / 36.1, k = 64 40.4 / 41.7; 2.4 tiles 36.7 / 37.8 and 41.6
+// / 42.8; 2.9 tiles (N = 3000, d = 4096) 44.9 / 43.3 and 57.0 / 55.5, (N =
+// 12205, d = 1024) 43.2 / 42.5 and 46.6 / 47.5.  k > 64 takes the columns
+// always (U's registers).
 template <int KS, bool HAS_E, bool GZ, bool ZB>
 static hipError_t launch_cols(int64_t N, int d, int k, int64_t V, const float* Zc,
                               const uint16_t* Zb, const int32_t* ids, const void* E, const void* U,
@@ -343,9 +351,10 @@ static hipError_t launch_cols(int64_t N, int d, int k, int64_t V, const float* Z
     const int64_t r = slots / nd < 1 ? 1 : slots / nd;
     return r < most ? r : most;
   };
-  int64_t nd = ((int64_t)d + kExpandBlockCols - 1) / kExpandBlockCols, ranges = ranges_of(nd, tiles);
+  int64_t nd = ((int64_t)d + kExpandBlockCols - 1) / kExpandBlockCols;
+  int64_t ranges = decompress_cols_ranges(d) < tiles ? decompress_cols_ranges(d) : tiles;
   if constexpr (KS <= 2) {
-    if (tiles <= 3 * ranges) {
+    if (4 * tiles <= 11 * ranges) {
       nd = d / kExpandCols;
       ranges = ranges_of(nd, (tiles + kExpandWaves - 1) / kExpandWaves);
       hipLaunchKernelGGL((decompress_cols_bf16<KS, HAS_E, GZ, ZB, true>), dim3((unsigned)(nd * ranges)),

@@ -39,6 +39,9 @@ hipError_t launch_factor_grad_f32(int64_t N, int64_t din, int64_t k, const float
 // kernels, and whether that grid is one round of blocks, at least 90 % full.
 int decompress_grid_split(int64_t blocks, int chunks);
 bool decompress_chunks_fill(int64_t N, int64_t d);
+// Token ranges that two blocks per compute unit leave the bf16 column kernel
+// (512 columns to a block).
+int64_t decompress_cols_ranges(int64_t d);
 // bf16 form of launch_decompress (same arguments; only where
 // decompress_uses_mfma holds and Z, E, U, Y are 16-byte aligned).
 hipError_t launch_decompress_bf16(int64_t N, int64_t d, int64_t k, int64_t V, const float* Z,

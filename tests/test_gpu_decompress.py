@@ -80,6 +80,30 @@ def test_float32_narrow_bases(N, d, k, wire):
     test_decompress_shapes(N, d, k, wire, "f32")
 
 
+# bf16, the chunk-staged kernel: wide bases of whole pieces up to its last
+# output sizes (k = 72: 2^24, k = 128: 5308416, twice with a full round), one
+# round of blocks for k <= 64, odd widths with long rows
+@pytest.mark.parametrize("N,d,k", [(1, 128, 72), (130, 256, 96), (300, 640, 120), (5184, 1024, 128),
+                                   (5185, 1024, 128), (4096, 2560, 128), (4096, 2560, 40), (4096, 2560, 51),
+                                   (2048, 5120, 64), (1024, 18432, 51)])
+@pytest.mark.parametrize("wire", ["f32", "bf16"])
+def test_chunk_staged_bf16(N, d, k, wire):
+    test_decompress_shapes(N, d, k, wire, "bf16")
+
+
+# gathered coordinates from 2^27 elements on, in the expansion's bits
+def test_gathered_coordinates_of_a_full_round():
+    N, d, k = 32700, 4224, 64
+    U = I.to_device(I.store(I.gaussian_orthonormal_basis(d, k, 3), "bf16"), "bf16", DEV)
+    T = torch.from_numpy(rand_coords(40, k, 5)).to(DEV)
+    ids = torch.from_numpy(np.random.default_rng(6).integers(0, 40, size=N).astype(np.int32)).to(DEV)
+    X0 = ssn.factored_embedding(ids, T, U)
+    rows = sample_rows(N, 400, 3)
+    assert torch.equal(X0, ssn.expand_grad(T[ids.long()].contiguous(), U))
+    check("factored", I.to_host(X0)[rows], O.expand_grad(I.to_host(T)[I.to_host(ids)[rows]], I.to_host(U)),
+          "bf16", "bf16out")
+
+
 @pytest.mark.parametrize("N,d,k", [(200, 256, 51), (13000, 640, 33), (200, 256, 100)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_non_finite_coordinates_stay_in_their_token(N, d, k, dtype):
