@@ -555,17 +555,19 @@ __global__ __launch_bounds__(64 * P) __attribute__((amdgpu_waves_per_eu(1, 2))) 
 // contiguous bytes of one U row) and Z rows are B fragments.  Z (fp32) is
 // split into bf16 hi + lo parts, two MFMAs each, which keeps ~fp32 accuracy.
 //
-// Block = 4 waves x 16 tokens.  d is walked in 128-wide chunks, every block
+// Block = 8 waves x 16 tokens.  d is walked in 64-wide chunks, every block
 // starting at its own rotated offset (spreads concurrent requests over HBM
-// channels).  Per chunk the 256 threads stage the chunk's U rows into LDS in
-// A-fragment order (double buffered, one barrier per chunk); each wave runs 8
+// channels).  Per chunk the 512 threads stage the chunk's U rows into LDS in
+// A-fragment order (double buffered, one barrier per chunk); each wave runs 4
 // MFMA tiles for its 16 tokens and parks the fp32 results in a wave-private,
-// XOR-swizzled LDS tile [16 tokens x 128 d].  The epilogue then reads that
-// tile back row-wise, adds E[ids] (loaded one chunk ahead, 256 contiguous
-// bytes of 4 rows per load instruction), rounds once to bf16, and stores 256
-// contiguous bytes of 4 rows per instruction.
+// XOR-swizzled LDS tile [16 tokens x 64 d].  The epilogue then reads that
+// tile back row-wise, adds E[ids] (loaded one chunk ahead, 128 contiguous
+// bytes of 8 rows per load instruction), rounds once to bf16, and stores 128
+// contiguous bytes of 8 rows per instruction (non-temporal), or SG = 2 chunks
+// together.
 // ===========================================================================
 constexpr int kDecompressDC = 64;
+constexpr int kDecompressTW = 8;       // waves (token tiles) per block
 
 // KM: 0 when k == 32*KS2; 1 when k % 8 == 0 (16-byte rows of U and Z, zero
 // groups past k); 2 for any other k: Z is read element by element, and each
@@ -574,31 +576,27 @@ constexpr int kDecompressDC = 64;
 // GZ: the coordinate row of token t is Z[ids[t]] (a gathered table of
 // coordinates, e.g. the factored embedding E U^T of section 4.1) instead of
 // Z[t]; used without the additive embedding.
-template <int KS2, bool HAS_E, int KM, int DC = kDecompressDC, int DSPLIT = 1, int TW = 4,
-          bool NTS = false, bool GZ = false, bool NTE = false, int PF = 1, int SG = 1,
-          int ROTG = 1>
-__global__ __launch_bounds__(64 * TW * DSPLIT) void decompress_mfma_bf16(
+template <int KS2, bool HAS_E, int KM, bool GZ, int SG>
+__global__ __launch_bounds__(64 * kDecompressTW) void decompress_mfma_bf16(
     const float* __restrict__ Zc, const int32_t* __restrict__ ids,
     const uint16_t* __restrict__ E, const uint16_t* __restrict__ U,
     uint16_t* __restrict__ Y, int64_t N, int d, int k, int64_t V,
     const uint16_t* __restrict__ Zb, int kz) {
-  static_assert(DC == 64 || DC == 128, "chunk of 64 or 128 d");
+  constexpr int DC = kDecompressDC;
   static_assert(KM >= 0 && KM <= 2, "k layout mode");
   static_assert(!(HAS_E && GZ), "gathered coordinates carry no additive embedding");
   constexpr bool KFULL32 = (KM == 0);
   constexpr int NT = DC / 16;                     // MFMA tiles per chunk
   constexpr int FR = NT * KS2 * kWave;            // A fragments per chunk
-  constexpr int PT = 64 * TW;                      // stager threads per part
+  constexpr int PT = 64 * kDecompressTW;          // threads
   constexpr int FPT = (FR + PT - 1) / PT;         // staged per thread (last round partial)
-  __shared__ u32x4 ufr[2][DSPLIT * FR];           // [buffer][part * FR + fragment]
-  __shared__ f32x4 stage[TW * DSPLIT][16 * (DC / 4)];  // [wave][token * DC/4 + cell ^ token]
+  __shared__ u32x4 ufr[2][FR];                    // [buffer][fragment]
+  __shared__ f32x4 stage[kDecompressTW][16 * (DC / 4)];  // [wave][token * DC/4 + cell ^ token]
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int n16 = lane & 15, g = lane >> 4;
-  // wave = part * TW + token tile: DSPLIT parts of d run side by side
-  const int part = DSPLIT == 1 ? 0 : wave / TW;
-  const int64_t tok0 = (int64_t)blockIdx.x * (16 * TW) + (wave % TW) * 16;
+  const int64_t tok0 = (int64_t)blockIdx.x * (16 * kDecompressTW) + wave * 16;
 
   // Z^T B fragments of this wave's 16 tokens.  Tokens past N take row N - 1
   // (here and in the epilogue), so their lanes recompute token N - 1 and
@@ -661,11 +659,10 @@ __global__ __launch_bounds__(64 * TW * DSPLIT) void decompress_mfma_bf16(
     erow[q] = HAS_E ? E + clamp_id(ids[t], V) * d + 8 * ec : nullptr;
   }
 
-  // U staging: thread tid stages fragments of part tid/PT.  Fragment f ->
-  // tile f/(KS2*64), K step (f/64)%KS2, lane position f%64 = 16*g' + m: row
-  // 16*tile + m, columns 32*s + 8*g'.
+  // U staging.  Fragment f -> tile f/(KS2*64), K step (f/64)%KS2, lane
+  // position f%64 = 16*g' + m: row 16*tile + m, columns 32*s + 8*g'.
   //  KM == 0 (k == 32*KS2): a chunk's 64 rows are one contiguous span of
-  //    64*k elements, so thread piece p = tid%PT + PT*q loads the 16 bytes at
+  //    64*k elements, so thread piece p = tid + PT*q loads the 16 bytes at
   //    8p of the span (a wave's load covers 1 KB of whole lines) and stores
   //    them to the fragment that holds them (row p/(k/8), 8-column group
   //    p%(k/8)).  Loading each fragment where it sits in U instead (16 rows
@@ -674,12 +671,11 @@ __global__ __launch_bounds__(64 * TW * DSPLIT) void decompress_mfma_bf16(
   // Threads past the last fragment load fragment FR - 1 again and do not
   // store it, and columns past k load column 0 and store zeros, so that the
   // loads, too, are unconditional.
-  const int spart = DSPLIT == 1 ? 0 : tid / PT, stid = DSPLIT == 1 ? tid : tid % PT;
   int srow[FPT], scol[FPT], sdst[FPT];
   bool son[FPT];
 #pragma unroll
   for (int q = 0; q < FPT; ++q) {
-    const int f0 = stid + PT * q;
+    const int f0 = tid + PT * q;
     son[q] = FR % PT == 0 || f0 < FR;          // compile-time when every thread stores
     const int f = son[q] ? f0 : FR - 1;
     if constexpr (KM == 0) {
@@ -727,54 +723,45 @@ __global__ __launch_bounds__(64 * TW * DSPLIT) void decompress_mfma_bf16(
                           : u32x4{0u, 0u, 0u, 0u};
         else
           v = (KFULL32 || scol[q] < k) ? u[q] : u32x4{0u, 0u, 0u, 0u};
-        ufr[buf][spart * FR + sdst[q]] = v;
+        ufr[buf][sdst[q]] = v;
       }
   };
-  // E rows of chunk j travel in ring slot j % (PF + 1), PF chunks ahead.
-  // SG > 1: the packed outputs of SG consecutive chunks are kept in
-  // registers and stored together (SG * DC * 2 contiguous bytes per row);
-  // then nch must be a multiple of R.
-  static_assert(PF == 1 || PF == 3 || PF == 7, "embedding prefetch depth");
-  static_assert(SG == 1 || SG == 2 || SG == 4 || SG == 8, "store group");
-  constexpr int R = (PF + 1) > SG ? (PF + 1) : SG;   // steps per unrolled group
-  u32x4 ering[PF + 1][NQ];
+  // E rows of chunk j travel in ring slot j % 2, a chunk ahead.  SG == 2: the
+  // packed outputs of two consecutive chunks are kept in registers and stored
+  // together (256 contiguous bytes per row); then nch must be even.
+  static_assert(SG == 1 || SG == 2, "store group");
+  u32x4 ering[2][NQ];
   u32x4 ypk[SG][NQ];
   auto load_e = [&](int c, u32x4(&eo)[NQ]) {
     if constexpr (HAS_E) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) eo[q] = ldg<NTE>(erow[q] + c * DC);
+      for (int q = 0; q < NQ; ++q) eo[q] = ldg<false>(erow[q] + c * DC);
     }
   };
 
   // blockIdx.y selects one of gridDim.y equal ranges of d (more blocks when
-  // there are few tokens); part p of the block walks chunks
-  // [(y*DSPLIT + p)*nch, +nch) of that range, rotated per block
-  const int nch = d / (DC * DSPLIT * (int)gridDim.y);
-  // rotation in units of ROTG chunks (when they divide nch)
-  const int rg = (ROTG > 1 && nch % ROTG == 0) ? ROTG : 1;
-  const int rot = (int)(blockIdx.x % (unsigned)(nch / rg)) * rg;
-  const int pbase = (int)blockIdx.y * DSPLIT;
-  auto chunk_of = [&](int p, int i) {
+  // there are few tokens), walked from a start rotated per block
+  const int nch = d / (DC * (int)gridDim.y);
+  const int rot = (int)(blockIdx.x % (unsigned)nch);
+  auto chunk = [&](int i) {
     const int x = i + rot;
-    return (pbase + p) * nch + (x < nch ? x : x - nch);
+    return (int)blockIdx.y * nch + (x < nch ? x : x - nch);
   };
-  auto chunk = [&](int i) { return chunk_of(part, i); };
   auto last = [&](int i) { return i < nch ? i : nch - 1; };
   f32x4* st = stage[wave];
 
-  // One chunk, i % R == B.  Order: loads for later chunks (U of chunk i + 2,
-  // E of chunk i + PF), barrier, MFMAs, epilogue stores, and only then the
+  // One chunk, i % 2 == B.  Order: loads for later chunks (U of chunk i + 2,
+  // E of chunk i + 1), barrier, MFMAs, epilogue stores, and only then the
   // LDS store of chunk i + 1's U, whose loads were issued one chunk earlier.
   // Loads and stores share one completion counter, so no wait in a chunk
   // covers the stores that chunk issued.
   auto body = [&](int i, auto Bc) {
     constexpr int B = decltype(Bc)::value;
-    constexpr int US = B & 1;
     const int c = chunk(i);
-    load_u(chunk_of(spart, last(i + 2)), ust[US]);
-    load_e(chunk(last(i + PF)), ering[(B + PF) % (PF + 1)]);
+    load_u(chunk(last(i + 2)), ust[B]);
+    load_e(chunk(last(i + 1)), ering[B ^ 1]);
     __syncthreads();
-    const u32x4* fr = ufr[US] + part * FR;
+    const u32x4* fr = ufr[B];
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) {
       f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -794,7 +781,7 @@ __global__ __launch_bounds__(64 * TW * DSPLIT) void decompress_mfma_bf16(
       const f32x4 bb = st[tl * (DC / 4) + ((2 * ec + 1) ^ tl)];
       float v[8] = {a[0], a[1], a[2], a[3], bb[0], bb[1], bb[2], bb[3]};
       if constexpr (HAS_E) {
-        const u32x4 e = ering[B % (PF + 1)][q];
+        const u32x4 e = ering[B][q];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
           v[2 * m] += lo_bf16(e[m]);
@@ -803,55 +790,31 @@ __global__ __launch_bounds__(64 * TW * DSPLIT) void decompress_mfma_bf16(
       }
       const u32x4 y = u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
                             pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-      if constexpr (SG == 1) stg<NTS>(yrow[q] + c * DC, y);
-      else ypk[B % SG][q] = y;
+      if constexpr (SG == 1) stg<true>(yrow[q] + c * DC, y);
+      else ypk[B][q] = y;
     }
-    if constexpr (SG > 1 && B % SG == SG - 1) {
+    if constexpr (SG == 2 && B == 1) {
 #pragma unroll
       for (int j = 0; j < SG; ++j) {
         const int cj = chunk(i - (SG - 1) + j);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) stg<NTS>(yrow[q] + cj * DC, ypk[j][q]);
+        for (int q = 0; q < NQ; ++q) stg<true>(yrow[q] + cj * DC, ypk[j][q]);
       }
     }
-    store_u(US ^ 1, ust[US ^ 1]);
-  };
-  auto group = [&](int i0, int n) {   // steps i0 .. i0 + n - 1 (n < R, i0 % R == 0, SG == 1)
-    body(i0, std::integral_constant<int, 0>{});
-    if (n > 1) body(i0 + 1, std::integral_constant<int, 1>{});
-    if constexpr (R > 2) {
-      if (n > 2) body(i0 + 2, std::integral_constant<int, 2 % R>{});
-      if (n > 3) body(i0 + 3, std::integral_constant<int, 3 % R>{});
-    }
-    if constexpr (R > 4) {
-      if (n > 4) body(i0 + 4, std::integral_constant<int, 4 % R>{});
-      if (n > 5) body(i0 + 5, std::integral_constant<int, 5 % R>{});
-      if (n > 6) body(i0 + 6, std::integral_constant<int, 6 % R>{});
-    }
+    store_u(B ^ 1, ust[B ^ 1]);
   };
 
-  load_u(chunk_of(spart, 0), ust[0]);
-  load_u(chunk_of(spart, last(1)), ust[1]);
-#pragma unroll
-  for (int j = 0; j < PF; ++j) load_e(chunk(last(j)), ering[j]);
+  load_u(chunk(0), ust[0]);
+  load_u(chunk(last(1)), ust[1]);
+  load_e(chunk(0), ering[0]);
   store_u(0, ust[0]);
-  const int nfull = nch - nch % R;
-  for (int i0 = 0; i0 < nfull; i0 += R) {
-    body(i0, std::integral_constant<int, 0>{});
-    body(i0 + 1, std::integral_constant<int, 1>{});
-    if constexpr (R > 2) {
-      body(i0 + 2, std::integral_constant<int, 2 % R>{});
-      body(i0 + 3, std::integral_constant<int, 3 % R>{});
-    }
-    if constexpr (R > 4) {
-      body(i0 + 4, std::integral_constant<int, 4 % R>{});
-      body(i0 + 5, std::integral_constant<int, 5 % R>{});
-      body(i0 + 6, std::integral_constant<int, 6 % R>{});
-      body(i0 + 7, std::integral_constant<int, 7 % R>{});
-    }
+  int i = 0;
+  for (; i + 1 < nch; i += 2) {
+    body(i, std::integral_constant<int, 0>{});
+    body(i + 1, std::integral_constant<int, 1>{});
   }
   if constexpr (SG == 1) {
-    if (nfull < nch) group(nfull, nch - nfull);
+    if (i < nch) body(i, std::integral_constant<int, 0>{});
   }
 }
 
@@ -1342,20 +1305,20 @@ template <int KS2, bool HAS_E, bool GZ, int KM>
 static hipError_t launch_decompress_km(int64_t N, int d, int k, int64_t V, const float* Zc,
                                        const int32_t* ids, const void* E, const void* U, void* Y,
                                        hipStream_t st, const uint16_t* Zb, int kz) {
-  constexpr int TW = 8;
+  constexpr int TW = kDecompressTW;
   const int64_t blocks = (N + 16 * TW - 1) / (16 * TW);
   const int chunks = d / kDecompressDC;
   const int gy = decompress_grid_split(blocks, chunks);
   const dim3 grid((unsigned)blocks, (unsigned)gy);
-  if (!HAS_E && (chunks / gy) % 2 == 0)
-    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, GZ, false,
-                                             1, 2>),
-                       grid, dim3(64 * TW), 0, st, Zc, ids, (const uint16_t*)E, (const uint16_t*)U,
-                       (uint16_t*)Y, N, d, k, V, Zb, kz);
-  else
-    hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, kDecompressDC, 1, TW, true, GZ>), grid,
-                       dim3(64 * TW), 0, st, Zc, ids, (const uint16_t*)E, (const uint16_t*)U,
-                       (uint16_t*)Y, N, d, k, V, Zb, kz);
+  if constexpr (!HAS_E) {
+    if ((chunks / gy) % 2 == 0) {
+      hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, GZ, 2>), grid, dim3(64 * TW), 0, st, Zc,
+                         ids, (const uint16_t*)E, (const uint16_t*)U, (uint16_t*)Y, N, d, k, V, Zb, kz);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((decompress_mfma_bf16<KS2, HAS_E, KM, GZ, 1>), grid, dim3(64 * TW), 0, st, Zc, ids,
+                     (const uint16_t*)E, (const uint16_t*)U, (uint16_t*)Y, N, d, k, V, Zb, kz);
   return hipGetLastError();
 }
 
