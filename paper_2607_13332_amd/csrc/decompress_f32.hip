@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64 * kExp32Waves, 2) void decompress_cols_f32(
     load_z(ptoken(0) * kz);
   }
   // ---- U: per K step 8 rows x 128 bytes an instruction, through a
-  // wave-private LDS tile (a wave's LDS operations complete in order) ----
+  // wave-private LDS tile ----
   f32x4 uraw[KS][UR];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
@@ -195,6 +195,7 @@ __global__ __launch_bounds__(64 * kExp32Waves, 2) void decompress_cols_f32(
       for (int e = 0; e < 4; ++e) v[e] = e < nz ? 0.f : v[e];
       ut[wave][((8 * r + (lane >> 3)) * UPITCH + 4 * (lane & 7)) / 4] = v;
     }
+    wave_lds_order();
 #pragma unroll
     for (int tt = 0; tt < NTL; ++tt) {
       const f32x4* src = &ut[wave][((NTL * n16 + tt) * UPITCH + 8 * g) / 4];
@@ -202,6 +203,7 @@ __global__ __launch_bounds__(64 * kExp32Waves, 2) void decompress_cols_f32(
       const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
       split3_bf16x8(v, ub[s][tt][0], ub[s][tt][1], ub[s][tt][2]);
     }
+    wave_lds_order();
   }
   store_z(0);
 

@@ -237,11 +237,12 @@ __global__ __launch_bounds__(64 * kExpandWaves, 2) void decompress_cols_bf16(
 #pragma unroll
     for (int s = 0; s < KS; ++s) park_u(s, ut[s]);
   } else {
-    // wave-private: a wave's LDS operations complete in order
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       park_u(s, ut[wave]);
+      wave_lds_order();
       take_u(s, ut[wave]);
+      wave_lds_order();
     }
   }
 #pragma unroll

@@ -682,10 +682,10 @@ __global__ __launch_bounds__(512) void decompress_f32_chunks(
 #pragma unroll
         for (int s = 0; s < 4; ++s) acc[tt] = mfma16x16x4f32(a[s], zf[q][s], acc[tt]);
       }
-    wave_lds_fence();
+    wave_lds_order();
 #pragma unroll
     for (int tt = 0; tt < 4; ++tt) sw[n16 * 16 + ((4 * tt + g) ^ n16)] = acc[tt];
-    wave_lds_fence();
+    wave_lds_order();
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const int r = 4 * m + g;
