@@ -214,11 +214,16 @@ def compress(X: torch.Tensor, ids: torch.Tensor, E: torch.Tensor, U: torch.Tenso
                          f"E{tuple(E.shape)} U{tuple(U.shape)}")
     if out is None:
         out = torch.empty((N, k), dtype=z_dtype, device=X.device)
-    t, g = X.dtype, X.get_device()
-    _check("ssn_compress_ex", lib().ssn_compress_ex(
-        _code(t), _code(z_dtype), N, d, k, V, _gpu(X, "X", X, g, t, 2),
-        _gpu(ids, "ids", X, g, torch.int32, 1), _gpu(E, "E", X, g, t, 2), _gpu(U, "U", X, g, t, 2), ldu,
-        _gpu(out, "out", X, g, z_dtype, 2), _stream(stream)))
+    try:
+        t, g = X.dtype, X.get_device()
+        status = lib().ssn_compress_ex(
+            _code(t), _code(z_dtype), N, d, k, V, _gpu(X, "X", X, g, t, 2),
+            _gpu(ids, "ids", X, g, torch.int32, 1), _gpu(E, "E", X, g, t, 2), _gpu(U, "U", X, g, t, 2),
+            ldu, _gpu(out, "out", X, g, z_dtype, 2), _stream(stream))
+    except AttributeError:            # not a tensor
+        _same_device(X, ids, E, U, out)
+        raise
+    _check("ssn_compress_ex", status)
     return out
 
 
@@ -241,12 +246,17 @@ def decompress(Z: torch.Tensor, ids: Optional[torch.Tensor], E: Optional[torch.T
             raise ValueError(f"shape mismatch E{tuple(E.shape)} ids{tuple(ids.shape)}")
     if out is None:
         out = torch.empty((N, d), dtype=t, device=Z.device)
-    zt, g = Z.dtype, Z.get_device()
-    _check("ssn_decompress_ex", lib().ssn_decompress_ex(
-        _code(t), _code(zt), N, d, k, V, _gpu(Z, "Z", Z, g, zt, 2),
-        None if ids is None else _gpu(ids, "ids", Z, g, torch.int32, 1),
-        None if E is None else _gpu(E, "E", Z, g, t, 2), _gpu(U, "U", Z, g, t, 2), ldu,
-        _gpu(out, "out", Z, g, t, 2), _stream(stream)))
+    try:
+        zt, g = Z.dtype, Z.get_device()
+        status = lib().ssn_decompress_ex(
+            _code(t), _code(zt), N, d, k, V, _gpu(Z, "Z", Z, g, zt, 2),
+            None if ids is None else _gpu(ids, "ids", Z, g, torch.int32, 1),
+            None if E is None else _gpu(E, "E", Z, g, t, 2), _gpu(U, "U", Z, g, t, 2), ldu,
+            _gpu(out, "out", Z, g, t, 2), _stream(stream))
+    except AttributeError:            # not a tensor
+        _same_device(Z, ids, E, U, out)
+        raise
+    _check("ssn_decompress_ex", status)
     return out
 
 
@@ -270,16 +280,21 @@ def project_grad(G: torch.Tensor, U: torch.Tensor, out: Optional[torch.Tensor] =
         raise ValueError(f"shape mismatch G{tuple(G.shape)} U{tuple(U.shape)}")
     if out is None:
         out = torch.empty((N, k), dtype=z_dtype, device=G.device)
-    t, g = G.dtype, G.get_device()
-    if workspace is None:
-        _check("ssn_project_grad_ex", lib().ssn_project_grad_ex(
+    try:
+        t, g = G.dtype, G.get_device()
+        if workspace is None:
+            _check("ssn_project_grad_ex", lib().ssn_project_grad_ex(
+                _code(t), _code(z_dtype), N, d, k, _gpu(G, "G", G, g, t, 2), _gpu(U, "U", G, g, t, 2),
+                ldu, _gpu(out, "out", G, g, z_dtype, 2), _stream(stream)))
+            return out
+        status = lib().ssn_project_grad_ws(
             _code(t), _code(z_dtype), N, d, k, _gpu(G, "G", G, g, t, 2), _gpu(U, "U", G, g, t, 2), ldu,
-            _gpu(out, "out", G, g, z_dtype, 2), _stream(stream)))
-        return out
-    _check("ssn_project_grad_ws", lib().ssn_project_grad_ws(
-        _code(t), _code(z_dtype), N, d, k, _gpu(G, "G", G, g, t, 2), _gpu(U, "U", G, g, t, 2), ldu,
-        _gpu(out, "out", G, g, z_dtype, 2), _gpu(workspace, "workspace", G, g, torch.uint8, 1),
-        workspace.numel(), _stream(stream)))
+            _gpu(out, "out", G, g, z_dtype, 2), _gpu(workspace, "workspace", G, g, torch.uint8, 1),
+            workspace.numel(), _stream(stream))
+    except AttributeError:            # not a tensor
+        _same_device(G, U, out, workspace)
+        raise
+    _check("ssn_project_grad_ws", status)
     return out
 
 
@@ -361,11 +376,16 @@ def compress_projected(X: torch.Tensor, ids: torch.Tensor, P: torch.Tensor, U: t
                          f"P{tuple(P.shape)} U{tuple(U.shape)}")
     if out is None:
         out = torch.empty((N, k), dtype=z_dtype, device=X.device)
-    t, g = X.dtype, X.get_device()
-    _check("ssn_compress_projected_ex", lib().ssn_compress_projected_ex(
-        _code(t), _code(z_dtype), N, d, k, V, _gpu(X, "X", X, g, t, 2),
-        _gpu(ids, "ids", X, g, torch.int32, 1), _gpu(P, "P", X, g, torch.float32, 2),
-        _gpu(U, "U", X, g, t, 2), ldu, _gpu(out, "out", X, g, z_dtype, 2), _stream(stream)))
+    try:
+        t, g = X.dtype, X.get_device()
+        status = lib().ssn_compress_projected_ex(
+            _code(t), _code(z_dtype), N, d, k, V, _gpu(X, "X", X, g, t, 2),
+            _gpu(ids, "ids", X, g, torch.int32, 1), _gpu(P, "P", X, g, torch.float32, 2),
+            _gpu(U, "U", X, g, t, 2), ldu, _gpu(out, "out", X, g, z_dtype, 2), _stream(stream))
+    except AttributeError:            # not a tensor
+        _same_device(X, ids, P, U, out)
+        raise
+    _check("ssn_compress_projected_ex", status)
     return out
 
 

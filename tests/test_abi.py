@@ -333,3 +333,14 @@ def test_binding_refuses_cpu_tensors_and_missing_library(ssn, monkeypatch):
     monkeypatch.setattr(ssn, "LIB_PATH", "/nonexistent/libssn.so")
     with pytest.raises(RuntimeError, match="not built"):
         ssn.lib()
+
+
+def test_wrapper_rejects_arrays(ssn):
+    # arrays have the shape of a tensor and a device of their own
+    import numpy as np
+    X, U, P = np.zeros((4, 8), np.float32), np.zeros((8, 2), np.float32), np.zeros((5, 2), np.float32)
+    ids, E = np.zeros(4, np.int32), np.zeros((5, 8), np.float32)
+    for call in (lambda: ssn.compress(X, ids, E, U), lambda: ssn.project_grad(X, U),
+                 lambda: ssn.compress_projected(X, ids, P, U)):
+        with pytest.raises(ValueError, match="different devices"):
+            call()
