@@ -339,6 +339,13 @@ __global__ __launch_bounds__(64 * W) void compress_f32_mfma(
 // (j, g) ends with coordinates KP j .. KP j + KP - 1 of tokens 4 g .. 4 g + 3.
 // Block = W waves x 16 tokens, every wave sweeping all of d (start rotated per
 // block).
+// A float32 MFMA rounds the running sum once per product, so one chain over d
+// errs by three times what the planes do (d = 512 .. 5120 4.1e-7 .. 1.28e-6
+// against 1.4e-7 .. 4.5e-7).  The products therefore go into NC chains: 8 over
+// all of d, added once at the end (d = 576 1.6e-7, 4096 4.1e-7, with smaller
+// largest errors than the planes'; 1 to 6 % longer than one chain), or, with
+// the registers of one tile, 4 over each chunk, added to the total once per
+// chunk (d = 256 9e-8, 4096 1.7e-7).
 // ===========================================================================
 template <int KP, bool HAS_E, bool HAS_P, bool SPAN, int W>
 __global__ __launch_bounds__(64 * W) void compress_f32_blocks(
@@ -346,7 +353,7 @@ __global__ __launch_bounds__(64 * W) void compress_f32_blocks(
     const float* __restrict__ U, float* __restrict__ Z, int64_t N, int d, int64_t V,
     const float* __restrict__ Pt, uint16_t* __restrict__ Zb, int kz, int ku) {
   static_assert(!(HAS_E && HAS_P), "the embedding is subtracted as rows or as projected rows");
-  constexpr int K = 16 * KP, DC = kF32Chunk;
+  constexpr int K = 16 * KP, DC = kF32Chunk, NC = KP == 1 ? 4 : 8;
   using Stage = UStage<K, 64 * W, SPAN>;
   constexpr int UP = Stage::UP, FPT = Stage::FPT;
   __shared__ __align__(16) float ut[2][DC * UP];
@@ -395,9 +402,12 @@ __global__ __launch_bounds__(64 * W) void compress_f32_blocks(
   };
   auto last = [&](int i) { return i < nch ? i : nch - 1; };
   f32x4* dw = dt[wave];
-  f32x4 acc[KP];
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 part[NC][KP], total = zero;
 #pragma unroll
-  for (int i = 0; i < KP; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int n = 0; n < NC; ++n)
+#pragma unroll
+    for (int h = 0; h < KP; ++h) part[n][h] = zero;
 
   auto body = [&](int i, auto Bc) {
     constexpr int B = decltype(Bc)::value;
@@ -419,9 +429,13 @@ __global__ __launch_bounds__(64 * W) void compress_f32_blocks(
         float b[KP];
         u_row<KP>(ub + (16 * q + 4 * g + s) * UP + KP * n16, b);
 #pragma unroll
-        for (int h = 0; h < KP; ++h) acc[h] = mfma16x16x4f32(a[s], b[h], acc[h]);
+        for (int h = 0; h < KP; ++h) {
+          f32x4& p = part[(4 * q + s) % NC][h];
+          p = mfma16x16x4f32(a[s], b[h], KP == 1 && q == 0 ? zero : p);
+        }
       }
     }
+    if constexpr (KP == 1) total += (part[0][0] + part[1][0]) + (part[2][0] + part[3][0]);
     stage.store(ut[B ^ 1], ust[B ^ 1]);
   };
 
@@ -436,6 +450,17 @@ __global__ __launch_bounds__(64 * W) void compress_f32_blocks(
   }
   if (i < nch) body(i, std::integral_constant<int, 0>{});
 
+  if constexpr (KP == 1) {
+    part[0][0] = total;
+  } else {
+#pragma unroll
+    for (int n = NC / 2; n > 0; n /= 2)
+#pragma unroll
+      for (int c = 0; c < n; ++c)
+#pragma unroll
+        for (int h = 0; h < KP; ++h) part[c][h] += part[c + n][h];
+  }
+
   // lane (j, g): coordinates KP j + h of tokens 4 g + r
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -445,7 +470,7 @@ __global__ __launch_bounds__(64 * W) void compress_f32_blocks(
     for (int h = 0; h < KP; ++h) {
       const int col = KP * n16 + h;
       if (col >= kz) continue;
-      float v = acc[h][r];
+      float v = part[0][h][r];
       if constexpr (HAS_P) v -= Pt[prow[r] + col];
       if (Zb)
         Zb[t * kz + col] = (uint16_t)f32_to_bf16(v);
@@ -599,7 +624,9 @@ __global__ __launch_bounds__(64 * PW) void compress_f32_split(
 // E[ids] added (loaded one chunk ahead), stored non-temporally.  Block = 8
 // waves x 16 tokens; a second grid dimension splits d
 // (decompress_grid_split).  Tokens past N recompute token N - 1 and store the
-// same bytes there.  GZ: the coordinate row of token t is Z[ids[t]].
+// same bytes there.  GZ: the coordinate row of token t is Z[ids[t]].  The
+// products of a tile go into NA chains, added at the end: one chain errs by up
+// to 1.01e-7 at k = 31, four by 6.6e-8 (1 to 4 % longer).
 // ===========================================================================
 template <int KQ, bool HAS_E, bool GZ, bool SPAN>
 __global__ __launch_bounds__(512) void decompress_f32_chunks(
@@ -607,7 +634,7 @@ __global__ __launch_bounds__(512) void decompress_f32_chunks(
     const float* __restrict__ U, float* __restrict__ Y, int64_t N, int d, int64_t V,
     const uint16_t* __restrict__ Zb, int kz, int ku) {
   static_assert(!(HAS_E && GZ), "gathered coordinates carry no additive embedding");
-  constexpr int K = 16 * KQ, DC = kF32Chunk, W = 8;
+  constexpr int K = 16 * KQ, DC = kF32Chunk, W = 8, NA = 2 * KQ;
   using Stage = UStage<K, 64 * W, SPAN>;
   constexpr int UP = Stage::UP, FPT = Stage::FPT;
   __shared__ __align__(16) float ut[2][DC * UP];
@@ -671,20 +698,31 @@ __global__ __launch_bounds__(512) void decompress_f32_chunks(
     load_e(chunk(last(i + 1)), ering[B ^ 1]);
     __syncthreads();
     const float* ub = ut[B];
-    f32x4 acc[4];
+    f32x4 acc[NA][4];
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) acc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int tt = 0; tt < 4; ++tt) acc[a][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < KQ; ++q)
 #pragma unroll
       for (int tt = 0; tt < 4; ++tt) {
         const f32x4 a = *(const f32x4*)(ub + (16 * tt + n16) * UP + 16 * q + 4 * g);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) acc[tt] = mfma16x16x4f32(a[s], zf[q][s], acc[tt]);
+        for (int s = 0; s < 4; ++s) {
+          f32x4& p = acc[(4 * q + s) % NA][tt];
+          p = mfma16x16x4f32(a[s], zf[q][s], p);
+        }
       }
+#pragma unroll
+    for (int n = NA / 2; n > 0; n /= 2)
+#pragma unroll
+      for (int a = 0; a < n; ++a)
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) acc[a][tt] += acc[a + n][tt];
     wave_lds_order();
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) sw[n16 * 16 + ((4 * tt + g) ^ n16)] = acc[tt];
+    for (int tt = 0; tt < 4; ++tt) sw[n16 * 16 + ((4 * tt + g) ^ n16)] = acc[0][tt];
     wave_lds_order();
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
@@ -775,20 +813,20 @@ static hipError_t launch_compress_f32_planes(int64_t N, int d, int64_t V, const 
 }
 
 // Where compress_f32_blocks runs (64-token blocks).  k <= 16 and up to 1024
-// tokens, where a few blocks wait for their loads and little else (N = 512, d =
-// 256, k = 8 projection 5.9 / 5.4 us, compress 6.5 / 6.0; N = 1500, d = 576
-// 9.8 / 11.3).  With a basis as wide as its tiles: the projection with up to one block per compute unit and k <= 80 (N
-// = 16384, d = 4096, planes against this: k = 16 58.9 / 46.2 us, 64 94 / 86; d =
-// 576, k = 80, N = 4096 21.5 / 18.4; k = 96 129 / 130 on both), or more blocks
-// and k <= 32 (N = 20000, d = 5120, k = 16 87 / 79; k = 64 158 / 180); compress
-// with more blocks and k <= 32 (N = 20000, d = 4096, k = 16 116 / 114, k = 32
-// 127 / 124; k = 64 145 / 177).
+// tokens, where a few blocks wait for their loads and little else (planes /
+// this: N = 512, d = 256, k = 8 projection 5.8 / 5.5 us, compress 6.5 / 6.1; N =
+// 900, d = 576, k = 16 9.0 / 7.8 and 10.0 / 8.9).  With a basis as wide as its
+// tiles: the projection with up to one block per compute unit and k <= 80 (N =
+// 16384, d = 4096 k = 16 49.3 / 46.7, 32 61.4 / 57.2, 64 91.2 / 89.5; N = 12000, d
+// = 2048, k = 80 61.0 / 56.3; k = 96 129 / 130), or k = 16 (N = 20000, d = 5120
+// 86.8 / 81.5; k = 32 103 / 106); compress at k = 16 with more blocks (N =
+// 20000, d = 4096 115 / 113; k = 32 127 / 124, but d = 2048 76.5 / 77.1).
 template <int KP>
 static bool compress_f32_uses_blocks(int64_t N, bool has_e, int kz, int ku) {
   if (KP == 1 && N <= 1024) return true;
   if (ku != 16 * KP || kz != ku) return false;
   const bool one = (N + 63) / 64 <= device_cu_count();
-  return has_e ? KP <= 2 && !one : KP <= 2 || (KP <= 5 && one);
+  return has_e ? KP == 1 && !one : KP == 1 || one;
 }
 
 template <int KP, bool SPAN>
@@ -798,7 +836,7 @@ static hipError_t launch_compress_f32_blocks(int64_t N, int d, int64_t V, const 
                                              int kz, int ku) {
   constexpr int W = 4;
   const dim3 grid((unsigned)((N + 16 * W - 1) / (16 * W)));
-  if constexpr (KP <= 2) {
+  if constexpr (KP == 1) {
     if (E) {
       hipLaunchKernelGGL((compress_f32_blocks<KP, true, false, SPAN, W>), grid, dim3(64 * W), 0, st, X,
                          ids, E, U, Z, N, d, V, P, Zb, kz, ku);

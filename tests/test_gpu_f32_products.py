@@ -117,3 +117,33 @@ def test_one_product_of_a_large_operand(op, scale):
     y = (1.0 + r.random(m)).astype(np.float32)
     ref = x[:, None].astype(np.float64) * y[None, :].astype(np.float64)
     assert np.abs(fn(x, y).astype(np.float64) / ref - 1.0).max() <= ONE
+
+
+# A running sum of L random terms that is rounded once per product errs by
+# 0.425 x 2^-24 sqrt(L / 2) of the result: a rounding is off by 2^-24 / (sqrt(3)
+# m) of a value of mantissa m, and the mean of 1 / m^2 over log-uniform m is 3 / (8
+# ln 2); the i-th partial sum has sqrt(i / L) of the last one's size.  n chains
+# divide that by sqrt(n): 8 chains (and the planes) stay below half of it, the
+# few chains of a short sum below three quarters.
+@pytest.mark.parametrize("op,N,d,k,part", [
+    ("project", 512, 256, 8, 0.5), ("compress", 512, 256, 8, 0.5), ("project", 900, 576, 16, 0.5),
+    ("compress", 20000, 1024, 16, 0.5), ("project", 4096, 576, 80, 0.5), ("project", 12300, 4096, 32, 0.5),
+    ("project", 16384, 2048, 64, 0.5), ("project", 20000, 1024, 32, 0.5), ("expand", 3000, 576, 24, 0.75),
+    ("expand", 1500, 1024, 31, 0.75)])
+def test_rounding_of_sums(op, N, d, k, part):
+    r = np.random.default_rng(11)
+    U = r.standard_normal((d, k)).astype(np.float32)
+    if op == "expand":
+        L, A, B = k, r.standard_normal((N, k)).astype(np.float32), U.T
+        out = ssn.expand_grad(gpu(A), gpu(U))
+    else:
+        L, A, B = d, r.standard_normal((N, d)).astype(np.float32), U
+        if op == "compress":
+            ids = torch.zeros(N, dtype=torch.int32, device=DEV)
+            out = ssn.compress(gpu(A), ids, torch.zeros((1, d), device=DEV), gpu(U))
+        else:
+            out = ssn.project_grad(gpu(A), gpu(U))
+    rows = np.arange(0, N, max(1, N // 2000))
+    ref = A[rows].astype(np.float64) @ B.astype(np.float64)
+    err = out.cpu().numpy()[rows].astype(np.float64) - ref
+    assert np.sqrt((err ** 2).mean() / (ref ** 2).mean()) <= part * 0.425 * 2.0 ** -24 * np.sqrt(L / 2)
