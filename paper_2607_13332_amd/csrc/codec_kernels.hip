@@ -1274,7 +1274,8 @@ hipError_t launch_project_ranges(int dtype, int64_t N, int64_t d, int64_t k, con
 // 1 when the blocks alone reach one per compute unit; else the smallest
 // divisor of the chunk count that leaves every block at least two chunks and
 // fills at least 90 % of the blocks' last round, else the smallest that
-// reaches one block per unit (96 blocks in 5 ranges of d = 5120 57.9 us, in 4
+// reaches one block per unit (measured for decompress at N = 12288, d = 5120,
+// before the column kernel took that shape: 96 blocks in 5 ranges 57.9 us, in 4
 // ranges 64.3 us).
 int decompress_grid_split(int64_t blocks, int chunks) {
   const int64_t cus = device_cu_count();

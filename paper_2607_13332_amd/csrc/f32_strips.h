@@ -17,9 +17,9 @@ namespace ssn {
 // Weight re-projection W <- U (U^T W) with float32 storage (the original SSN's
 // step after each optimizer update, sections 4.1 and 6.1).
 //
-// Products: every float32 operand is split exactly into three bf16 planes
-// (split3_bf16x8) and a product takes the six plane pairs that leave
-// out at most 2^-24 of it, on the bf16 matrix cores: 6 instructions of 16x16x32 (96
+// Products: every float32 operand is split into three bf16 planes that hold
+// its 24 bits (split3_bf16x8) and a product takes the six plane pairs that
+// leave out at most 2^-24 of it, on the bf16 matrix cores: 6 instructions of 16x16x32 (96
 // cycles) do the work of 8 of 16x16x4 in float32 (256 cycles).  The five
 // small pairs of a K step are summed on their own and added to the running
 // sum once, so a running sum is rounded twice per 32 products (the float32
@@ -50,9 +50,9 @@ namespace ssn {
 //
 // Bound: HBM, W read once and written once.  Measured on MI355X against the
 // kernel that multiplied float32 operands and passed W through LDS: 4 x
-// (5120^2, 5120 x 18432) at k = 51 1508 -> 761 us (5.07 TB/s, the rate of a
-// large copy), error against 64 bits 1.3e-6 -> 5.1e-7; 4 x (4096^2, 4096 x
-// 14336) at k = 64 821 -> 550 us.
+// (5120^2, 5120 x 18432) at k = 51 1597 -> 771 us (5.0 TB/s, the rate of a
+// large copy); 4 x (4096^2, 4096 x 14336) at k = 64 845 -> 544 us; error
+// against 64 bits at 2048^2, k = 51 3.2e-7 -> 1.3e-7.
 //
 // FG: the reparameterized layer's factor gradient (section 4.1, Eq. (3)),
 // dZp = H^T GT, with H [N, din] as the single matrix of the batch, GT [N, k]
@@ -550,7 +550,8 @@ static hipError_t launch_weights_f32_cfg(ColumnBatchF32& cb, const float* U, int
 // 138; 4096 x (4096 + 14336) 309 -> 174; 5120 x (5120 + 18432), k = 51 547
 // -> 237; k = 128, 2048^2 82 -> 67 and 4 x (5120^2, 5120 x 18432) 3737 ->
 // 1461; k <= 16, whose products are few, 4 x (2048^2, 2048 x 7168) 112 ->
-// 110, 4 x (4096^2, 4096 x 14336) 399 -> 418 (five waves on 231 units).
+// 110, 4 x (4096^2, 4096 x 14336) 400 -> 416 (five waves on 231 units; other
+// strip shapes and an even spread over 256 units 412 to 466).
 template <int KT, bool FG>
 hipError_t launch_weights_f32_kt(ColumnBatchF32& cb, const float* U, int rows, int k, float* fg_out,
                                  hipStream_t st) {
